@@ -291,6 +291,9 @@ template <class T> __device__ __forceinline__ void stg(T *base, unsigned idx, T 
   *(T *)((char *)base + idx * (unsigned)sizeof(T)) = v;
 }
 
+// Element of an array of up to 2^31 elements (64-bit byte address).
+template <class T> __device__ __forceinline__ T ldg64(const T *base, unsigned idx) { return base[(size_t)idx]; }
+
 // Raw buffer access: one descriptor (SGPRs) per array slice (a population or a scalar
 // field, under 4 GiB since Q N < 2^31 elements) and a 32-bit byte offset per lane, so the
 // neighbours of a cell share offset registers and no load needs 64-bit address arithmetic.
@@ -523,22 +526,23 @@ void step_kernel(KArgs<typename Prec<PREC>::R> a) {
         if (a.mx.on) {
           MixPoint<R> mc;
           mix_point<R>(a.mx, a.th, phi0, rho0, pim, mc, mu_c, cp_c);
+#pragma unroll
           for (int d = 0; d < D; ++d) {
 #pragma unroll
             for (int side = 0; side < 2; ++side) {
-              const int sn = status(d, side == 0 ? 1 : -1);
-              if (sn != ST_FLUID && sn != ST_INLET) continue;
+              // a neighbour across a solid, wall or outlet face is replaced by the cell itself
+              // and the face's weight is zero, so that the loads need no branch
+              const int sn = INTER ? ST_FLUID : status(d, side == 0 ? 1 : -1);
+              const R hf = sn == ST_FLUID || sn == ST_INLET ? R(0.5) : R(0);
+              const unsigned mq = sn == ST_FLUID ? un + (unsigned)off[d][side == 0 ? 3 : 1] : un;
               MixPoint<R> mn;
               R vn[NSV];
-              if (sn == ST_FLUID) {
-                const unsigned mq = un + (unsigned)off[d][side == 0 ? 3 : 1];
 #pragma unroll
-                for (int q = 0; q < NS; ++q) vn[q] = (R)bld<Sc>(slice(sin_ + (size_t)q * N), mq);
-                R mu_n, cp_n;
-                mix_point<R>(a.mx, a.th, vn, density<NS, R>(a.th, vn, pim), pim, mn, mu_n, cp_n);
-              } else {
-#pragma unroll
-                for (int q = 0; q < NS; ++q) vn[q] = phin[q];
+              for (int q = 0; q < NS; ++q) vn[q] = (R)bld<Sc>(slice(sin_ + (size_t)q * N), mq);
+              R mu_n, cp_n;
+              mix_point<R>(a.mx, a.th, vn, density<NS, R>(a.th, vn, pim), pim, mn, mu_n, cp_n);
+              if (!INTER && sn == ST_INLET) {
+                vn[0] = phin[0];
                 mn.kap = a.mx.in_kap;
 #pragma unroll
                 for (int k = 0; k < 6; ++k) {
@@ -547,15 +551,15 @@ void step_kernel(KArgs<typename Prec<PREC>::R> a) {
                   mn.Y[k] = a.mx.in_Y[k];
                 }
               }
-              R_s[0] += R(0.5) * (mc.kap + mn.kap) * (vn[0] - phi0[0]);
+              R_s[0] += hf * (mc.kap + mn.kap) * (vn[0] - phi0[0]);
               R J[6], Js = R(0);
 #pragma unroll
               for (int k = 0; k < 6; ++k) {
-                J[k] = -R(0.5) * (mc.coef[k] + mn.coef[k]) * (mn.X[k] - mc.X[k]);
+                J[k] = -hf * (mc.coef[k] + mn.coef[k]) * (mn.X[k] - mc.X[k]);
                 Js += J[k];
               }
 #pragma unroll
-              for (int k = 0; k < 5; ++k) R_s[1 + k] -= J[k] - R(0.5) * (mc.Y[k] + mn.Y[k]) * Js;
+              for (int k = 0; k < 5; ++k) R_s[1 + k] -= J[k] - hf * (mc.Y[k] + mn.Y[k]) * Js;
             }
           }
         }
@@ -610,11 +614,37 @@ void step_kernel(KArgs<typename Prec<PREC>::R> a) {
             uw_in[0] *= sc; uw_in[1] *= sc; uw_in[2] *= sc;
           }
         }
-        R uo[3] = {R(0), R(0), R(0)};
-        bool has_out = false;
+        // Which population of which cell each link reads: its own opposite one where the
+        // source is solid or beyond a face, else population i of the source.  One load per
+        // link from a selected address, all of them in flight together: as loads inside
+        // the branches of each case they ran one after another, a memory round trip each
+        // (these and the stencil loads below: 2-D flame 1024x256 FP64 20.2 -> 18.5 us per
+        // step, its 1230x310 FP32 twin 16.5 -> 15.0 us, a 128x128x256 burner with mixture
+        // transport and curved walls 0.452 -> 0.428 ms).
+        St raw[Q];
+        auto beyond = [&](int i, int st) -> bool {          // r - c_i lies through a face of status st
+          const int c[3] = {cx(i), cy(i), D == 3 ? cz(i) : 0};
+          bool hit = false;
 #pragma unroll
-        for (int d = 0; d < D; ++d) has_out |= a.face[2 * d] == ST_OUTLET || a.face[2 * d + 1] == ST_OUTLET;
-        if (has_out) {
+          for (int d = 0; d < D; ++d)
+            if (c[d] != 0) hit |= code[d][2 - c[d]] == st;
+          return hit;
+        };
+        auto source = [&](int i) -> unsigned {              // r - c_i
+          return un + (unsigned)(off[0][2 - cx(i)] + off[1][2 - cy(i)] + (D == 3 ? off[2][2 - cz(i)] : 0));
+        };
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+          const bool own = beyond(i, ST_SOLID) || beyond(i, ST_INLET) || beyond(i, ST_OUTLET) || ((gw >> i) & 1);
+          const unsigned e = own ? (unsigned)(Q - 1 - i) * (unsigned)N + un : (unsigned)i * (unsigned)N + source(i);
+          raw[i] = ldg64(pin, e);
+        }
+        const R invP0 = a.invP0;
+        R uo[3] = {R(0), R(0), R(0)};
+        bool at_out = false;
+#pragma unroll
+        for (int d = 0; d < D; ++d) at_out |= code[d][1] == ST_OUTLET || code[d][3] == ST_OUTLET;
+        if (at_out) {                                       // momentum of the cell's own populations
 #pragma unroll
           for (int j = 0; j < Q; ++j) {
             const R gj = decode<R>(bld<St>(slice(pin + (size_t)j * N), un));
@@ -626,53 +656,40 @@ void step_kernel(KArgs<typename Prec<PREC>::R> a) {
           uo[0] *= f; uo[1] *= f; uo[2] *= f;
         }
         const R uo2 = uo[0] * uo[0] + uo[1] * uo[1] + uo[2] * uo[2];
-        const R invP0 = a.invP0;
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
-          const int c[3] = {cx(i), cy(i), D == 3 ? cz(i) : 0};
-          bool wall = false, inl = false, outl = false;
+          const R g = decode<R>(raw[i]);
+          const bool wall = beyond(i, ST_SOLID), inl = beyond(i, ST_INLET), outl = beyond(i, ST_OUTLET);
+          const R cui = R(cx(i)) * uw_in[0] + R(cy(i)) * uw_in[1] + (D == 3 ? R(cz(i)) * uw_in[2] : R(0));
+          const R cuo = R(cx(i)) * uo[0] + R(cy(i)) * uo[1] + (D == 3 ? R(cz(i)) * uo[2] : R(0));
+          const R vin = g + R(2.0 * wgt<Q>(i)) * rho_in * cui * invP0;
+          const R vout = -g + R(2.0 * wgt<Q>(i)) * ((R(a.outlet_P) + rho0 * (cuo * cuo * R(1.5) - uo2 * R(0.5))) * invP0 - R(1));
+          gh[i] = wall ? g : inl ? vin : outl ? vout : g;
+        }
+        if constexpr (FULL) {
+          if (a.lvl && (gw & linkmask)) {
+            // curved walls: interpolated bounce-back on the links cut inside the domain, the
+            // wall at the fraction q of the link to r - c_i; the second value of each link
+            // and the wall distances are again selected loads
+            const double l0 = a.lvl[n];
 #pragma unroll
-          for (int d = 0; d < D; ++d) {
-            if (c[d] == 0) continue;
-            const int cd = code[d][2 - c[d]];
-            wall |= cd == ST_SOLID;
-            inl |= cd == ST_INLET;
-            outl |= cd == ST_OUTLET;
-          }
-          const bool solid_src = (gw >> i) & 1;
-          const int io = Q - 1 - i;
-          if (wall || (!inl && !outl && solid_src)) {
-            const R gopp = decode<R>(bld<St>(slice(pin + (size_t)io * N), un));
-            gh[i] = gopp;
-            if (FULL && !wall && a.lvl) {
-              // interpolated bounce-back, the wall at the fraction q of the link to r - c_i
-              const unsigned ms = un + (unsigned)(off[0][2 - c[0]] + off[1][2 - c[1]] + (D == 3 ? off[2][2 - c[2]] : 0));
-              const double l0 = a.lvl[n];
-              const R qf = (R)(l0 / (l0 - a.lvl[ms]));
-              if (qf < R(0.5)) {
-                bool ahead_fluid = !((gw >> io) & 1);        // r + c_i is a fluid node
-#pragma unroll
-                for (int d = 0; d < D; ++d)
-                  if (c[d] != 0 && code[d][2 + c[d]] >= 0) ahead_fluid = false;
-                if (ahead_fluid) {
-                  const unsigned ma = un + (unsigned)(off[0][2 + c[0]] + off[1][2 + c[1]] + (D == 3 ? off[2][2 + c[2]] : 0));
-                  gh[i] = lerp(decode<R>(bld<St>(slice(pin + (size_t)io * N), ma)), gopp, R(2) * qf);
-                }
-              } else {
-                const R h = fdiv(R(1), R(2) * qf);
-                gh[i] = gopp * h + (R(1) - h) * decode<R>(bld<St>(slice(pin + (size_t)i * N), un));
-              }
+            for (int i = 0; i < Q; ++i) {
+              const int io = Q - 1 - i;
+              if (i == io) continue;
+              const bool cut = ((gw >> i) & 1) && !beyond(i, ST_SOLID) && !beyond(i, ST_INLET) && !beyond(i, ST_OUTLET);
+              const double ls = a.lvl[cut ? source(i) : un];
+              const R qf = cut ? (R)(l0 / (l0 - ls)) : R(0.5);
+              const bool near = qf < R(0.5);
+              // r + c_i is a fluid node of the domain
+              const bool ahead = !((gw >> io) & 1) && !beyond(io, ST_SOLID) && !beyond(io, ST_INLET) && !beyond(io, ST_OUTLET);
+              const unsigned e = near ? (unsigned)io * (unsigned)N + (ahead ? source(io) : un) : (unsigned)i * (unsigned)N + un;
+              const R g2 = decode<R>(ldg64(pin, e));
+              const R gopp = gh[i];
+              const R h = fdiv(R(1), R(2) * qf);
+              const R vnear = ahead ? lerp(g2, gopp, R(2) * qf) : gopp;
+              const R vfar = gopp * h + (R(1) - h) * g2;
+              gh[i] = cut ? (near ? vnear : vfar) : gopp;
             }
-          } else if (inl) {
-            const R cu = R(c[0]) * uw_in[0] + R(c[1]) * uw_in[1] + R(c[2]) * uw_in[2];
-            gh[i] = decode<R>(bld<St>(slice(pin + (size_t)io * N), un)) + R(2.0 * wgt<Q>(i)) * rho_in * cu * invP0;
-          } else if (outl) {
-            const R cu = R(c[0]) * uo[0] + R(c[1]) * uo[1] + R(c[2]) * uo[2];
-            gh[i] = -decode<R>(bld<St>(slice(pin + (size_t)io * N), un)) +
-                    R(2.0 * wgt<Q>(i)) * ((R(a.outlet_P) + rho0 * (cu * cu * R(1.5) - uo2 * R(0.5))) * invP0 - R(1));
-          } else {
-            const unsigned m = un + (unsigned)(off[0][2 - c[0]] + off[1][2 - c[1]] + (D == 3 ? off[2][2 - c[2]] : 0));
-            gh[i] = decode<R>(bld<St, 2>(slice(pin + (size_t)i * N), m));
           }
         }
       }
@@ -722,7 +739,13 @@ void step_kernel(KArgs<typename Prec<PREC>::R> a) {
             // chosen once per axis instead of values per scalar); diffusion and density are
             // symmetric in the two, grad rho takes the sign back
             const unsigned mdw = up ? mp1 : mm1, muw = up ? mm1 : mp1;
-            R vp1[NSV], vm1[NSV];
+            R vp1[NSV], vm1[NSV], fp2[NSV], fm2[NSV];
+            // general path: the four neighbours of every scalar by unconditional loads, a
+            // point that is not a fluid node replaced by the cell itself, so that they are all
+            // in flight together (loads inside branches waited for one another)
+            const unsigned ip1 = sp1 == ST_FLUID ? mp1 : un, im1 = sm1 == ST_FLUID ? mm1 : un;
+            const unsigned ip2 = sp1 == ST_FLUID && sp2 == ST_FLUID ? mp2 : un;
+            const unsigned im2 = sm1 == ST_FLUID && sm2 == ST_FLUID ? mm2 : un;
 #pragma unroll
             for (int q = 0; q < NS; ++q) {
               const Sc *sq = sin_ + (size_t)q * N;
@@ -730,8 +753,14 @@ void step_kernel(KArgs<typename Prec<PREC>::R> a) {
                 vp1[q] = (R)bld<Sc>(slice(sq), mdw);
                 vm1[q] = (R)bld<Sc>(slice(sq), muw);
               } else {
-                vp1[q] = sp1 == ST_FLUID ? (R)bld<Sc>(slice(sq), mp1) : sp1 == ST_INLET ? phin[q] : phi0[q];
-                vm1[q] = sm1 == ST_FLUID ? (R)bld<Sc>(slice(sq), mm1) : sm1 == ST_INLET ? phin[q] : phi0[q];
+                vp1[q] = (R)bld<Sc>(slice(sq), ip1);
+                vm1[q] = (R)bld<Sc>(slice(sq), im1);
+                if (!EXTRACT) {
+                  fp2[q] = (R)bld<Sc>(slice(sq), ip2);
+                  fm2[q] = (R)bld<Sc>(slice(sq), im2);
+                }
+                if (sp1 == ST_INLET) vp1[q] = phin[q];
+                if (sm1 == ST_INLET) vm1[q] = phin[q];
               }
             }
             // curved walls: mirror images of solid cells at -1 / +1 (c1), of the stencil
@@ -812,13 +841,13 @@ void step_kernel(KArgs<typename Prec<PREC>::R> a) {
                   vU2 = (R)bld<Sc>(slice(sq), mfar);
                 } else {
                   R vm2, vp2;
-                  if (sm1 == ST_FLUID) vm2 = sm2 == ST_FLUID ? (R)bld<Sc>(slice(sq), mm2) : sm2 == ST_INLET ? phin[q] : vm1[q];
+                  if (sm1 == ST_FLUID) vm2 = sm2 == ST_FLUID ? fm2[q] : sm2 == ST_INLET ? phin[q] : vm1[q];
                   else vm2 = sm1 == ST_SOLID ? vp1[q] : sm1 == ST_INLET ? phin[q] : v0;
-                  if (sp1 == ST_FLUID) vp2 = sp2 == ST_FLUID ? (R)bld<Sc>(slice(sq), mp2) : sp2 == ST_INLET ? phin[q] : vp1[q];
+                  if (sp1 == ST_FLUID) vp2 = sp2 == ST_FLUID ? fp2[q] : sp2 == ST_INLET ? phin[q] : vp1[q];
                   else vp2 = sp1 == ST_SOLID ? vm1[q] : sp1 == ST_INLET ? phin[q] : v0;
-                  if (c2m) vm2 = p2m <= R(1) ? lerp(v0, vp1[q], p2m) : lerp(vp1[q], (R)bld<Sc>(slice(sq), mp2), p2m - R(1));
+                  if (c2m) vm2 = p2m <= R(1) ? lerp(v0, vp1[q], p2m) : lerp(vp1[q], fp2[q], p2m - R(1));
                   else if (c3m) vm2 = lerp(vm1[q], v0, w3m);
-                  if (c2p) vp2 = p2p <= R(1) ? lerp(v0, vm1[q], p2p) : lerp(vm1[q], (R)bld<Sc>(slice(sq), mm2), p2p - R(1));
+                  if (c2p) vp2 = p2p <= R(1) ? lerp(v0, vm1[q], p2p) : lerp(vm1[q], fm2[q], p2p - R(1));
                   else if (c3p) vp2 = lerp(vp1[q], v0, w3p);
                   vU2 = up ? vm2 : vp2;
                 }
