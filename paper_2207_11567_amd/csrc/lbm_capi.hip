@@ -28,7 +28,7 @@ struct lbm_solver {
   int Q, NS, D, prec, nblocks;
   int *flag;
   double *sums;
-  double *partials;   // block records of lbm_step: [nblocks] interior, then [list blocks]
+  double *partials;   // block records of lbm_step: [nblocks] tiles, then [list blocks]
   double *aux;        // block records of field extraction, flame surface and objective
   int *cells;         // linear indices of the boundary cells (the step's list half)
   int ncells;         // their number
@@ -78,6 +78,10 @@ static int n_scalars(int physics) {
 static size_t pop_elem(int prec) { return prec == LBM_FP64 ? 8 : prec == LBM_FP32 ? 4 : 2; }
 static size_t scal_elem(int prec) { return prec == LBM_FP64 ? 8 : 4; }
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
+
+// Blocks of a split D2Q9 step that update its listed boundary cells: a multiple of 8, so that
+// the tiles' blocks keep their XCDs.
+static int list_blocks(long long ncells) { return (int)(((ncells + 255) / 256 + 7) / 8 * 8); }
 
 struct Layout {
   long long N;
@@ -234,9 +238,8 @@ static lbm_status validate(const lbm_params *p, Layout *L, std::string &err, std
   L->NS = NS;
   L->D = Dm;
   L->nblocks = (int)((N + 255) / 256);
-  // step records (interior tiles, then list blocks, each at most nblocks), then those of
-  // the other reductions
-  const int nrec = 3 * L->nblocks;
+  // step records (tiles, then list blocks), then those of the other reductions
+  const int nrec = 2 * L->nblocks + list_blocks(N);
   L->pop_bytes = (size_t)Q * N * pop_elem(p->precision);
   L->scal_bytes = (size_t)NS * N * scal_elem(p->precision);
   L->off_flag = 0;
@@ -404,22 +407,38 @@ static hipError_t build_cell_list(lbm_solver *s) {
 }
 
 // One step from a.pop_in / a.scal_in, either as one instance over every cell or split into
-// the interior instance over the tile grid and the list instance over the boundary cells.
-// The split pays where the all-cell instance carries boundary code that costs the interior
-// cells: curved walls (the FULL instance; its list half is FULL) and, on large grids, the
-// steps with transported scalars (their stencil ghost rules are most of that code); with
-// mixture transport both halves are FULL instances; with observables (statistics, probes)
-// the step stays one FULL instance.  The isothermal and
-// passive steps measured slower as interior instances, and on small grids the second
-// kernel adds a pass of latency.  The interior half writes block records [0, nblocks), the
-// list half the records after them.
+// the interior cells of the tile grid and the listed boundary cells.  The split pays where
+// the all-cell instance carries boundary code that costs the interior cells: curved walls
+// (FULL list) and, on large grids, the steps with two or more transported scalars (their
+// stencil ghost rules are most of that code).  The isothermal and passive steps measured
+// slower as interior instances.  Block records: the tiles, then the list blocks.
+// D2Q9 runs both kinds in one launch, observables included, where the tiles need more than
+// one pass over the chip (256 CUs of 4 resident blocks in FP64, 8 in FP32): within one pass
+// the step takes the latency of its longest wave and the extra blocks only add to it.
+// us per step, one instance / split: FP64 flame 1024x256 (1024 tiles) 19.1 / 22.4, chamber
+// 1250x250 (1221) 26.8 / 24.2, flame 1800x400 (2813) 43.9 / 34.7, chamber 2500x500 70.8 / 57.9
+// (67.3 as two kernels on two streams), with statistics 87.0 / 75.0; FP32 flame 1230x310
+// (1490) 15.2 / 17.9, 1800x400 (2813) 24.9 / 20.7, 2048x512 31.9 / 27.9 (50.8 on two streams).
+// D3Q27 runs them as two kernels on two streams from 4096 tiles on (in one kernel the
+// boundary code's registers cost the interior cells their waves: reacting box 0.86 ->
+// 1.02 ms), and its steps with observables stay one FULL instance.
 static hipError_t launch_step_pass(lbm_solver *s, const StepArgs &a0) {
   StepArgs a = a0;
   a.partials = s->partials;
-  const bool split = !(a.stats || a.probe_out) && (a.lvl || (s->NS >= 2 && s->nblocks >= 4096));
+  const bool observed = a.stats || a.probe_out;
+  const int one_pass = s->prec == LBM_FP64 ? 1024 : 2048;
+  const bool large = s->Q == 9 ? s->nblocks > one_pass : s->nblocks >= 4096;
+  const bool split = (s->Q == 9 || !observed) && (a.lvl || (s->NS >= 2 && large));
   if (!split) {
     s->nrec = s->nblocks;
     return launch(s, LAUNCH_STEP, a);
+  }
+  if (s->Q == 9) {
+    a.cells = s->cells;
+    a.ncells = s->ncells;
+    a.nlb = list_blocks(s->ncells);
+    s->nrec = s->nblocks + a.nlb;
+    return launch(s, LAUNCH_STEP_SPLIT, a);
   }
   hipError_t e = hipSuccess;
   s->nrec = s->nblocks;
@@ -441,8 +460,7 @@ static hipError_t launch_step_pass(lbm_solver *s, const StepArgs &a0) {
   e = hipEventRecord(s->ev_fork, s->stream);
   if (e == hipSuccess) e = hipStreamWaitEvent(s->side, s->ev_fork, 0);
   if (e != hipSuccess) return e;
-  if (s->Q == 9) e = launch_d2q9(s->prec, s->NS, LAUNCH_STEP_LIST, b, nlb, s->side, nullptr, nullptr, nullptr);
-  else e = launch_d3q27(s->prec, s->NS, LAUNCH_STEP_LIST, b, nlb, s->side, nullptr, nullptr, nullptr);
+  e = launch_d3q27(s->prec, s->NS, LAUNCH_STEP_LIST, b, nlb, s->side, nullptr, nullptr, nullptr);
   if (e == hipSuccess) e = hipEventRecord(s->ev_join, s->side);
   if (e == hipSuccess) e = launch(s, LAUNCH_STEP_INTERIOR, a);
   // join: later work on the caller's stream sees both halves
@@ -569,7 +587,7 @@ lbm_status lbm_create(const lbm_params *p, void *stream, void *pop_a, void *pop_
   s->flag = (int *)(s->work + L.off_flag);
   s->sums = (double *)(s->work + L.off_sums);
   s->partials = (double *)(s->work + L.off_partials);
-  s->aux = s->partials + (size_t)2 * L.nblocks * NSUM;
+  s->aux = s->partials + (size_t)(L.nblocks + list_blocks(L.N)) * NSUM;
   s->cells = (int *)(s->work + L.off_cells);
   s->ncells = 0;
   s->nrec = L.nblocks;

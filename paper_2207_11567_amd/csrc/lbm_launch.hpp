@@ -7,10 +7,14 @@
 namespace lbm {
 
 // LAUNCH_STEP: every cell in one instance (FULL with curved walls, observables or mixture
-// transport); LAUNCH_STEP_INTERIOR / LAUNCH_STEP_LIST: the two halves of a split step
-// (interior cells on the tile grid, FULL with mixture transport; then the listed boundary
-// cells, FULL with curved walls or mixture transport).
-enum LaunchKind { LAUNCH_STEP = 0, LAUNCH_EXTRACT = 1, LAUNCH_INIT = 2, LAUNCH_STEP_INTERIOR = 3, LAUNCH_STEP_LIST = 4 };
+// transport); LAUNCH_STEP_SPLIT (D2Q9): a.nlb blocks of listed boundary cells and nblocks
+// tiles of interior cells in one launch; LAUNCH_STEP_INTERIOR / LAUNCH_STEP_LIST (D3Q27): the
+// two halves of a split step (interior cells, FULL with mixture transport; then the listed
+// boundary cells, FULL with curved walls or mixture transport).
+enum LaunchKind {
+  LAUNCH_STEP = 0, LAUNCH_EXTRACT = 1, LAUNCH_INIT = 2, LAUNCH_STEP_INTERIOR = 3, LAUNCH_STEP_LIST = 4,
+  LAUNCH_STEP_SPLIT = 5
+};
 
 // Returns hipSuccess or the launch error.  nblocks covers N cells with 256 threads.
 hipError_t launch_d2q9(int prec, int ns, int kind, const StepArgs &a, int nblocks, hipStream_t st,
@@ -48,6 +52,13 @@ int collision_instance(const StepArgs &a) {
   return (Q == 27 && ((R)a.wh != R(1) || a.p4)) ? COLL_CUM : COLL_CUM1;
 }
 
+// Every face periodic and no solid cell: no cell needs boundary code.
+inline bool without_boundaries(const StepArgs &a) {
+  bool free = !a.geom;
+  for (int f = 0; f < 6; ++f) free = free && a.face[f] < 0;
+  return free;
+}
+
 template <int Q, int PREC, int NS, bool FULL, int MODE>
 hipError_t launch_step(const StepArgs &a, int nblocks, hipStream_t st) {
   using R = typename Prec<PREC>::R;
@@ -77,6 +88,21 @@ hipError_t launch_step(const StepArgs &a, int nblocks, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <int PREC, int NS, bool LFULL, bool IFULL, int IMODE>
+hipError_t launch_split(const StepArgs &a, int nblocks, hipStream_t st) {
+  using R = typename Prec<PREC>::R;
+  const dim3 grid(nblocks + a.nlb), block(256);
+  if (collision_instance<9, PREC>(a) == COLL_BGK)
+    hipLaunchKernelGGL((split_kernel<PREC, NS, LFULL, IFULL, COLL_BGK, IMODE, false>), grid, block, 0, st, to_kargs<R>(a));
+  else if (!IFULL && a.pull_cached)
+    hipLaunchKernelGGL((split_kernel<PREC, NS, LFULL, IFULL, COLL_CUM1, IMODE, !IFULL>), grid, block, 0, st,
+                       to_kargs<R>(a));
+  else
+    hipLaunchKernelGGL((split_kernel<PREC, NS, LFULL, IFULL, COLL_CUM1, IMODE, false>), grid, block, 0, st,
+                       to_kargs<R>(a));
+  return hipGetLastError();
+}
+
 template <int Q, int PREC, int NS>
 hipError_t launch_one(int kind, const StepArgs &a, int nblocks, hipStream_t st, const double *Ph,
                       const double *u, const double *scal) {
@@ -84,17 +110,40 @@ hipError_t launch_one(int kind, const StepArgs &a, int nblocks, hipStream_t st, 
   const bool full = a.lvl || a.stats || a.probe_out || a.mix;
   switch (kind) {
     case LAUNCH_STEP:
-      return full ? launch_step<Q, PREC, NS, true, MODE_ALL>(a, nblocks, st)
-                  : launch_step<Q, PREC, NS, false, MODE_ALL>(a, nblocks, st);
+      if (full) return launch_step<Q, PREC, NS, true, MODE_ALL>(a, nblocks, st);
+      // no boundary anywhere: no boundary code (us per step, all-cell / free instance: vortex
+      // 128^2 FP64 6.0 / 4.8, HIT 100^3 FP16 storage 29.3 / 28.3, 128^3 FP32 89.2 / 88.0).  FP32
+      // populations beyond the Infinity Cache measured the other way: 256^3 655 / 666
+      if (without_boundaries(a) && !(PREC == 1 && a.pull_cached))
+        return a.band_rows ? launch_step<Q, PREC, NS, false, MODE_FREE>(a, nblocks, st)
+                           : launch_step<Q, PREC, NS, false, MODE_FREE_LIN>(a, nblocks, st);
+      return launch_step<Q, PREC, NS, false, MODE_ALL>(a, nblocks, st);
+    case LAUNCH_STEP_SPLIT:      // interior cells FULL with observables or mixture transport
+      if constexpr (Q == 9) {
+        const bool ifull = a.stats || a.probe_out || a.mix;
+        if (a.band_rows)
+          return ifull  ? launch_split<PREC, NS, true, true, MODE_INTERIOR>(a, nblocks, st)
+                 : full ? launch_split<PREC, NS, true, false, MODE_INTERIOR>(a, nblocks, st)
+                        : launch_split<PREC, NS, false, false, MODE_INTERIOR>(a, nblocks, st);
+        return ifull  ? launch_split<PREC, NS, true, true, MODE_INTERIOR_LIN>(a, nblocks, st)
+               : full ? launch_split<PREC, NS, true, false, MODE_INTERIOR_LIN>(a, nblocks, st)
+                      : launch_split<PREC, NS, false, false, MODE_INTERIOR_LIN>(a, nblocks, st);
+      }
+      return hipErrorInvalidValue;
     case LAUNCH_STEP_INTERIOR:   // on the 64x4 tile grid when it fits, else on linear tiles
-      if (a.band_rows)
-        return a.mix ? launch_step<Q, PREC, NS, true, MODE_INTERIOR>(a, nblocks, st)
-                     : launch_step<Q, PREC, NS, false, MODE_INTERIOR>(a, nblocks, st);
-      return a.mix ? launch_step<Q, PREC, NS, true, MODE_INTERIOR_LIN>(a, nblocks, st)
-                   : launch_step<Q, PREC, NS, false, MODE_INTERIOR_LIN>(a, nblocks, st);
+      if constexpr (Q == 27) {
+        if (a.band_rows)
+          return a.mix ? launch_step<Q, PREC, NS, true, MODE_INTERIOR>(a, nblocks, st)
+                       : launch_step<Q, PREC, NS, false, MODE_INTERIOR>(a, nblocks, st);
+        return a.mix ? launch_step<Q, PREC, NS, true, MODE_INTERIOR_LIN>(a, nblocks, st)
+                     : launch_step<Q, PREC, NS, false, MODE_INTERIOR_LIN>(a, nblocks, st);
+      }
+      return hipErrorInvalidValue;
     case LAUNCH_STEP_LIST:
-      return (a.lvl || a.mix) ? launch_step<Q, PREC, NS, true, MODE_LIST>(a, nblocks, st)
-                   : launch_step<Q, PREC, NS, false, MODE_LIST>(a, nblocks, st);
+      if constexpr (Q == 27)
+        return (a.lvl || a.mix) ? launch_step<Q, PREC, NS, true, MODE_LIST>(a, nblocks, st)
+                                : launch_step<Q, PREC, NS, false, MODE_LIST>(a, nblocks, st);
+      return hipErrorInvalidValue;
     case LAUNCH_EXTRACT:   // no collision on the extract path
       if (full)
         hipLaunchKernelGGL((step_kernel<Q, PREC, NS, true, true, COLL_CUM1, MODE_ALL>), dim3(nblocks), dim3(256), 0,

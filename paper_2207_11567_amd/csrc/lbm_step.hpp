@@ -30,12 +30,14 @@ namespace lbm {
 constexpr int NSUM = 9;
 // collision operator compiled into a step instance
 enum : int { COLL_CUM1 = 0, COLL_CUM = 1, COLL_BGK = 2 };
-// cells a step instance updates: every cell (64x4 tile grid when it fits, else linear
+// cells that step_cells updates: every cell (64x4 tile grid when it fits, else linear
 // 256-cell tiles), the interior cells only (the code of boundaries, solids and curved walls
 // is not compiled in; on the tile grid, where a wave's y and z are scalars, or on linear
 // tiles for grids the tiles do not fit), or the cells of a list (one thread per listed
-// cell: the cells the interior instance leaves)
-enum : int { MODE_ALL = 0, MODE_INTERIOR = 1, MODE_LIST = 2, MODE_INTERIOR_LIN = 3 };
+// cell: the cells the interior code leaves); or every cell of a domain without boundaries
+// (all faces periodic, no solids: nothing but interior cells, on the tile grid or on linear
+// tiles)
+enum : int { MODE_ALL = 0, MODE_INTERIOR = 1, MODE_LIST = 2, MODE_INTERIOR_LIN = 3, MODE_FREE = 4, MODE_FREE_LIN = 5 };
 
 // Host-side description of one launch (double precision constants).
 struct Thermo {
@@ -64,8 +66,9 @@ struct StepArgs {
   double transport[32];  // binary D0 (15), c_p a_k (6), b_k (6), exponents of mu and D
   double mix_in[19];   // inlet transport point: lambda, rho D_k W_k/W (6), X_k (6), Y_k (6)
   double *f_P, *f_rho, *f_u, *f_scal;   // field outputs (extract mode)
-  const int *cells;    // MODE_LIST: linear indices of the cells to update
+  const int *cells;    // split step: linear indices of the boundary cells
   int ncells;
+  int nlb;             // blocks that update them (a multiple of 8)
   int nx, ny, nz;
   long long N;
   int face[6];         // ST_* code of each face, -1 for periodic
@@ -104,7 +107,7 @@ template <class R> struct KArgs {
   int probe[8];
   double *f_P, *f_rho, *f_u, *f_scal;
   const int *cells;
-  int ncells;
+  int ncells, nlb;     // split step: listed boundary cells and the blocks that update them
   int nx, ny, nz, N;
   int face[6];
   long long step;
@@ -121,6 +124,13 @@ template <class R> struct KArgs {
   MixT<R> mx;
 };
 
+// The step kernels read their arguments where the launch put them (constant memory, scalar
+// loads at each use): a parameter handed on by reference is first copied field by field, all
+// of it loaded up front into scalar registers that the long kernels then spill.
+template <class R> __device__ __forceinline__ const KArgs<R> &kernel_args() {
+  return *(const KArgs<R> *)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
 template <class R> KArgs<R> to_kargs(const StepArgs &a) {
   KArgs<R> k;
   k.pop_in = a.pop_in; k.pop_out = a.pop_out; k.scal_in = a.scal_in; k.scal_out = a.scal_out;
@@ -129,7 +139,7 @@ template <class R> KArgs<R> to_kargs(const StepArgs &a) {
   for (int j = 0; j < 8; ++j) k.probe[j] = a.probe[j];
   k.kap = (R)a.kappa;
   k.f_P = a.f_P; k.f_rho = a.f_rho; k.f_u = a.f_u; k.f_scal = a.f_scal;
-  k.cells = a.cells; k.ncells = a.ncells;
+  k.cells = a.cells; k.ncells = a.ncells; k.nlb = a.nlb;
   k.nx = a.nx; k.ny = a.ny; k.nz = a.nz; k.N = (int)a.N;
   for (int f = 0; f < 6; ++f) k.face[f] = a.face[f];
   k.step = a.step; k.collision = a.collision; k.remap = a.remap; k.band_rows = a.band_rows;
@@ -192,6 +202,16 @@ template <> struct GeomWord<9> { using T = uint32_t; };
 // bit Q+1+2d (+1): the cell at +2 e_d (-2 e_d) is solid.
 template <int Q> __host__ __device__ constexpr int bit_self() { return Q; }
 template <int Q> __host__ __device__ constexpr int bit_far(int d, int neg) { return Q + 1 + 2 * d + neg; }
+
+// Links (one bit each) whose source lies one cell further along axis d, at -1 (side 0) or +1.
+template <int Q> __host__ __device__ constexpr unsigned links_from(int d, int side) {
+  unsigned m = 0;
+  for (int i = 0; i < Q; ++i) {
+    const int c = d == 0 ? cx(i) : d == 1 ? cy(i) : Q == 27 ? cz(i) : 0;
+    if (c == (side == 0 ? 1 : -1)) m |= 1u << i;
+  }
+  return m;
+}
 
 // XCD-aware block order: hardware hands consecutive workgroups to the 8 XCDs in turn;
 // remapping gives each XCD a contiguous slab of cells so that halo rows shared between
@@ -374,708 +394,63 @@ __device__ __forceinline__ double w_over_T(const ThermoT<R> &t, const R (&v)[NS 
 // rate one (D3Q27; any rate on D2Q9), COLL_CUM general cumulant rates, COLL_BGK the BGK
 // test mode.  Each instance holds one operator, so the registers of the unused ones do not
 // count against the production path.
+// The cells of one block of a step: red gets each thread's contribution to the FP64 sums,
+// the return value is the block's place among its kind (tile, or list block).
+template <int Q, int PREC, int NS, bool EXTRACT, bool FULL, int COLL, int MODE, bool PULLC>
+__device__ __forceinline__ int step_cells(const KArgs<typename Prec<PREC>::R> &a, int block, int nblocks,
+                                          double (&red)[NSUM]) {
+#include "lbm_step_cells.inc"
+  return tile;
+}
+
+// One kind of cell per launch: every cell, or one half of a split step of D3Q27 (interior
+// tiles, or the listed boundary cells, which run beside them on a side stream).
 // The FP32-arithmetic two-step D3Q27 step (FP32 or FP16 storage) asks for four waves per
 // SIMD (at most 128 VGPRs): its allocation otherwise lands a few registers above that, at
 // three waves; the few spilled values cost less than the lost wave (measured 9 % faster on
 // the reacting box in both storage precisions, 12 % for the interior half of the step
-// with mixture-averaged transport).
+// with mixture-averaged transport).  Its list half asks for the same, so that one of its
+// waves fits the place that an interior wave leaves.  The all-cell D3Q27 instances ask for the
+// waves that their interior cells can use: the scheduler otherwise spends registers on the
+// loads in flight that only the boundary cells issue.
 template <int Q, int PREC, int NS, bool EXTRACT, bool FULL, int COLL, int MODE>
 constexpr int step_waves_per_eu() {
-  return (Q == 27 && PREC != 0 && NS == 6 && !EXTRACT && COLL == COLL_CUM1 && MODE != MODE_LIST &&
-          (!FULL || MODE == MODE_INTERIOR || MODE == MODE_INTERIOR_LIN))
-             ? 4
-             : 1;
+  if (Q != 27 || EXTRACT || COLL != COLL_CUM1) return 1;
+  if (MODE == MODE_LIST) return PREC != 0 && NS == 6 ? (FULL ? 3 : 4) : 1;
+  if (MODE == MODE_ALL) {
+    if (PREC == 0) return NS == 0 ? (FULL ? 4 : 5) : NS == 1 ? (FULL ? 3 : 4) : NS == 2 ? 2 : 1;
+    return NS == 0 ? (FULL ? 6 : 8) : NS == 1 ? (FULL ? 5 : 6) : NS == 2 ? (FULL ? 4 : 5) : (FULL ? 3 : 4);
+  }
+  return PREC != 0 && NS == 6 ? 4 : 1;
 }
 template <int Q, int PREC, int NS, bool EXTRACT, bool FULL, int COLL, int MODE, bool PULLC = false>
 __global__ __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(step_waves_per_eu<Q, PREC, NS, EXTRACT, FULL, COLL, MODE>())))
 void step_kernel(KArgs<typename Prec<PREC>::R> a) {
-  using P = Prec<PREC>;
-  using St = typename P::St;
-  using R = typename P::R;
-  using Sc = typename P::Sc;
-  using GW = typename GeomWord<Q>::T;
-  constexpr int D = Lat<Q>::D;
-  constexpr int NSV = NS > 0 ? NS : 1;
-  constexpr R s = R(1.0 / 3.0);
-  constexpr bool INTER = MODE == MODE_INTERIOR || MODE == MODE_INTERIOR_LIN;   // interior cells only
-  // the plain interior instance takes y and z as scalars (the FULL one keeps them per lane:
-  // as scalars its register pressure spills more)
-  constexpr bool UNIYZ = MODE == MODE_INTERIOR && !FULL;
-
-  // Interior instance: the wave runs at a raised priority until its populations and cell
-  // scalars are loaded and the velocity is formed, so that waves about to issue loads
-  // are not starved by waves deep in their arithmetic (reacting box 0.869 -> 0.860 ms;
-  // keeping it raised through the scalar stencils too was slower, 0.883 ms).
-  if constexpr (INTER) __builtin_amdgcn_s_setprio(2);
-  const int tile = tile_of_block(blockIdx.x, gridDim.x, a.remap);
-  // Banded tile order: 64x4-cell tiles, visited band of rows by band, and inside a band
-  // plane by plane, so the +-1 and +-2 planes of the scalar stencils were touched a few
-  // dozen tiles earlier and are still in L2.
-  int n, x, y, z;
-  bool listed = true;
-  if constexpr (MODE == MODE_LIST) {
-    const int idx = (int)blockIdx.x * (int)blockDim.x + (int)threadIdx.x;
-    listed = idx < a.ncells;
-    n = listed ? a.cells[idx] : 0;
-    const int nxy = a.nx * a.ny;
-    z = n / nxy;
-    const int rem = n - z * nxy;
-    y = rem / a.nx;
-    x = rem - y * a.nx;
-  } else if (MODE == MODE_INTERIOR || (MODE == MODE_ALL && a.band_rows)) {
-    const int nxt = a.nx >> 6, bt = a.band_rows >> 2;
-    const int per_plane = nxt * bt, per_band = per_plane * a.nz;
-    const int band = tile / per_band, r = tile - band * per_band;
-    const int zz = r / per_plane, r2 = r - zz * per_plane;
-    const int xt = r2 / bt, ys = r2 - xt * bt;
-    x = (xt << 6) + ((int)threadIdx.x & 63);
-    y = band * a.band_rows + (ys << 2) + ((int)threadIdx.x >> 6);
-    z = zz;
-    if constexpr (UNIYZ) {
-      // a wave is 64 cells of one row of one plane: y and z are the same in every lane,
-      // so their offsets are scalar values
-      y = __builtin_amdgcn_readfirstlane(y);
-      z = __builtin_amdgcn_readfirstlane(z);
-    }
-    n = x + a.nx * (y + a.ny * z);
-  } else {
-    n = tile * (int)blockDim.x + (int)threadIdx.x;
-    const int nxy = a.nx * a.ny;
-    z = n / nxy;
-    const int rem = n - z * nxy;
-    y = rem / a.nx;
-    x = rem - y * a.nx;
-  }
   double red[NSUM] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-  const int N = a.N;
-  const unsigned un = (unsigned)n;
-  const St *__restrict__ pin = (const St *)a.pop_in;
-  St *__restrict__ pout = (St *)a.pop_out;
-  const Sc *__restrict__ sin_ = (const Sc *)a.scal_in;
-  Sc *__restrict__ sout = (Sc *)a.scal_out;
-
-  bool active = listed && n < N;
-  const GW gw = active && a.geom ? ((const GW *)a.geom)[n] : GW(0);
-  if constexpr (INTER)
-    active = active && gw == GW(0) && !near_face(x, a.nx, a.face[0], a.face[1]) &&
-             !near_face(y, a.ny, a.face[2], a.face[3]) && !near_face(z, a.nz, a.face[4], a.face[5]);
-  if (active) {
-    const int nxy = a.nx * a.ny;
-    if (!INTER && (gw & (GW(1) << bit_self<Q>()))) {
-      if (!EXTRACT) {
-#pragma unroll
-        for (int i = 0; i < Q; ++i) pout[i * N + n] = pin[i * N + n];
-#pragma unroll
-        for (int k = 0; k < NS; ++k) sout[k * N + n] = sin_[k * N + n];
-      } else {
-        if (a.f_P) a.f_P[n] = 0.0;
-        if (a.f_rho) a.f_rho[n] = 0.0;
-        if (a.f_u)
-#pragma unroll
-          for (int d = 0; d < D; ++d) a.f_u[d * N + n] = 0.0;
-        if (a.f_scal)
-#pragma unroll
-          for (int k = 0; k < NS; ++k) a.f_scal[k * N + n] = (double)sin_[k * N + n];
-      }
-    } else {
-      // neighbour offsets (relative linear index) and face codes for k = -2..2 per axis
-      int off[3][5], code[3][5];
-      axis_offsets(x, a.nx, a.face[0], a.face[1], 1, off[0], code[0]);
-      axis_offsets(y, a.ny, a.face[2], a.face[3], a.nx, off[1], code[1]);
-      if (D == 3) {
-        axis_offsets(z, a.nz, a.face[4], a.face[5], nxy, off[2], code[2]);
-      } else {
-#pragma unroll
-        for (int k = 0; k < 5; ++k) {
-          off[2][k] = 0;
-          code[2][k] = -1;
-        }
-      }
-      // status of the axis neighbours at -2, -1, +1, +2
-      auto status = [&](int d, int k) -> int {
-        const int c = code[d][k + 2];
-        if (c >= 0) return c;
-        const int b = k == 1 ? link_from_plus<Q>(d) : k == -1 ? link_from_minus<Q>(d) : bit_far<Q>(d, k < 0 ? 1 : 0);
-        return (gw >> b) & 1 ? ST_SOLID : ST_FLUID;
-      };
-
-      // ---------------------------------------------------------------- cell scalars, rho
-      // closed domain: density scaled by pi = P_th/P_th(0); q = dln(pi)/dt of this level
-      R pim = R(1), qn = R(0);
-      if (a.thermo) {
-        pim = (R)a.thermo[0];
-        qn = (R)a.thermo[1];
-      }
-      R phi0[NSV], phin[NSV];
-#pragma unroll
-      for (int k = 0; k < NSV; ++k) { phi0[k] = R(0); phin[k] = R(a.phi_in[k]); }
-#pragma unroll
-      for (int k = 0; k < NS; ++k) phi0[k] = (R)bld<Sc>(slice(sin_ + (size_t)k * N), un);
-      const R rho0 = NS > 0 ? density<NS, R>(a.th, phi0, pim) : R(a.th.rho_ref);
-      const R irho0 = fdiv(R(1), rho0);            // every later division by rho uses it
-      const R rho_in = NS > 0 ? density<NS, R>(a.th, phin, pim) : R(a.th.rho_ref);
-
-      // mixture-averaged diffusion (Hirschfelder-Curtiss fluxes with the correction flux,
-      // lambda grad T), formed before the populations are pulled to keep registers free
-      R R_s[NSV];
-#pragma unroll
-      for (int k = 0; k < NSV; ++k) R_s[k] = R(0);
-      R mu_c = R(0), cp_c = R(1);
-      if constexpr (FULL && NS == 6) {
-        if (a.mx.on) {
-          MixPoint<R> mc;
-          mix_point<R>(a.mx, a.th, phi0, rho0, pim, mc, mu_c, cp_c);
-#pragma unroll
-          for (int d = 0; d < D; ++d) {
-#pragma unroll
-            for (int side = 0; side < 2; ++side) {
-              // a neighbour across a solid, wall or outlet face is replaced by the cell itself
-              // and the face's weight is zero, so that the loads need no branch
-              const int sn = INTER ? ST_FLUID : status(d, side == 0 ? 1 : -1);
-              const R hf = sn == ST_FLUID || sn == ST_INLET ? R(0.5) : R(0);
-              const unsigned mq = sn == ST_FLUID ? un + (unsigned)off[d][side == 0 ? 3 : 1] : un;
-              MixPoint<R> mn;
-              R vn[NSV];
-#pragma unroll
-              for (int q = 0; q < NS; ++q) vn[q] = (R)bld<Sc>(slice(sin_ + (size_t)q * N), mq);
-              R mu_n, cp_n;
-              mix_point<R>(a.mx, a.th, vn, density<NS, R>(a.th, vn, pim), pim, mn, mu_n, cp_n);
-              if (!INTER && sn == ST_INLET) {
-                vn[0] = phin[0];
-                mn.kap = a.mx.in_kap;
-#pragma unroll
-                for (int k = 0; k < 6; ++k) {
-                  mn.coef[k] = a.mx.in_coef[k];
-                  mn.X[k] = a.mx.in_X[k];
-                  mn.Y[k] = a.mx.in_Y[k];
-                }
-              }
-              R_s[0] += hf * (mc.kap + mn.kap) * (vn[0] - phi0[0]);
-              R J[6], Js = R(0);
-#pragma unroll
-              for (int k = 0; k < 6; ++k) {
-                J[k] = -hf * (mc.coef[k] + mn.coef[k]) * (mn.X[k] - mc.X[k]);
-                Js += J[k];
-              }
-#pragma unroll
-              for (int k = 0; k < 5; ++k) R_s[1 + k] -= J[k] - hf * (mc.Y[k] + mn.Y[k]) * Js;
-            }
-          }
-        }
-      }
-
-      // ---------------------------------------------------------------- pull (Eq. 1)
-      R gh[Q];
-      const bool border = code[0][1] >= 0 || code[0][3] >= 0 || code[1][1] >= 0 || code[1][3] >= 0 ||
-                          (D == 3 && (code[2][1] >= 0 || code[2][3] >= 0));
-      constexpr GW linkmask = (GW(1) << Q) - GW(1);
-      if (INTER || (!border && !(gw & linkmask))) {
-        // PULLC (grids larger than the Infinity Cache): ordinary cached loads.  A wave's 64
-        // shifted values of a population with c_x != 0 straddle a cache line that the
-        // neighbouring tile in x reads too, and with streaming loads that line was often
-        // gone again (256^3 FP32 step: 0.688 -> 0.656 ms, HBM reads 1.08 -> 1.00 of the
-        // algorithmic ones).  Grids that fit keep streaming loads, which leave the cache
-        // to the freshly written populations the next step reads (cached: 4-12 % slower).
-        // Each pulled value is read once per step, so only the line that a shifted
-        // population (c_x != 0) shares with the neighbouring tile benefits from the cache:
-        // populations with c_x = 0 stream in every instance (reacting box 0.847 -> 0.842
-        // ms, HIT 256^3 FP32 0.660 -> 0.656 ms).
-        constexpr int PULL_AUX = PULLC ? 0 : 2;
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
-          if constexpr (UNIYZ) {
-            // the wave-uniform y/z part of the offset moves the slice's base (scalar
-            // arithmetic); the lanes add only the x part (three distinct offsets)
-            const long long yz = (long long)off[1][2 - cy(i)] + (D == 3 ? off[2][2 - cz(i)] : 0);
-            const St *base = (const St *)((const char *)pin + ((long long)i * N + yz) * (long long)sizeof(St));
-            if (cx(i) == 0) gh[i] = decode<R>(bld<St, 2>(slice(base), un));
-            else gh[i] = decode<R>(bld<St, PULL_AUX>(slice(base), un + (unsigned)off[0][2 - cx(i)]));
-          } else {
-            const unsigned m = un + (unsigned)(off[0][2 - cx(i)] + off[1][2 - cy(i)] + (D == 3 ? off[2][2 - cz(i)] : 0));
-            if (cx(i) == 0) gh[i] = decode<R>(bld<St, 2>(slice(pin + (size_t)i * N), m));
-            else gh[i] = decode<R>(bld<St, PULL_AUX>(slice(pin + (size_t)i * N), m));
-          }
-        }
-      } else if constexpr (!INTER) {
-        // boundary cell: bounce-back, moving-wall inlet, anti-bounce-back outlet
-        R uw_in[3] = {R(a.inlet_u[0]), R(a.inlet_u[1]), R(a.inlet_u[2])};
-        if (a.inlet_noise != 0.0) {
-          int fa = -1;
-#pragma unroll
-          for (int d = 0; d < D; ++d)
-            if (a.face[2 * d] == ST_INLET || a.face[2 * d + 1] == ST_INLET) fa = d;
-          if (fa >= 0) {
-            const int c3[3] = {x, y, z};
-            const int o0 = fa == 0 ? 1 : 0, o1 = fa == 2 ? 1 : 2;
-            const double xi = splitmix_xi(a.seed, (unsigned long long)c3[o0], (unsigned long long)c3[o1],
-                                          (unsigned long long)a.step);
-            const R sc = R(1.0 + a.inlet_noise * xi);
-            uw_in[0] *= sc; uw_in[1] *= sc; uw_in[2] *= sc;
-          }
-        }
-        // Which population of which cell each link reads: its own opposite one where the
-        // source is solid or beyond a face, else population i of the source.  One load per
-        // link from a selected address, all of them in flight together: as loads inside
-        // the branches of each case they ran one after another, a memory round trip each
-        // (these and the stencil loads below: 2-D flame 1024x256 FP64 20.2 -> 18.5 us per
-        // step, its 1230x310 FP32 twin 16.5 -> 15.0 us, a 128x128x256 burner with mixture
-        // transport and curved walls 0.452 -> 0.428 ms).
-        St raw[Q];
-        auto beyond = [&](int i, int st) -> bool {          // r - c_i lies through a face of status st
-          const int c[3] = {cx(i), cy(i), D == 3 ? cz(i) : 0};
-          bool hit = false;
-#pragma unroll
-          for (int d = 0; d < D; ++d)
-            if (c[d] != 0) hit |= code[d][2 - c[d]] == st;
-          return hit;
-        };
-        auto source = [&](int i) -> unsigned {              // r - c_i
-          return un + (unsigned)(off[0][2 - cx(i)] + off[1][2 - cy(i)] + (D == 3 ? off[2][2 - cz(i)] : 0));
-        };
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
-          const bool own = beyond(i, ST_SOLID) || beyond(i, ST_INLET) || beyond(i, ST_OUTLET) || ((gw >> i) & 1);
-          const unsigned e = own ? (unsigned)(Q - 1 - i) * (unsigned)N + un : (unsigned)i * (unsigned)N + source(i);
-          raw[i] = ldg64(pin, e);
-        }
-        const R invP0 = a.invP0;
-        R uo[3] = {R(0), R(0), R(0)};
-        bool at_out = false;
-#pragma unroll
-        for (int d = 0; d < D; ++d) at_out |= code[d][1] == ST_OUTLET || code[d][3] == ST_OUTLET;
-        if (at_out) {                                       // momentum of the cell's own populations
-#pragma unroll
-          for (int j = 0; j < Q; ++j) {
-            const R gj = decode<R>(bld<St>(slice(pin + (size_t)j * N), un));
-            uo[0] += R(cx(j)) * gj;
-            uo[1] += R(cy(j)) * gj;
-            if (D == 3) uo[2] += R(cz(j)) * gj;
-          }
-          const R f = R(3) * R(a.P0) * irho0;
-          uo[0] *= f; uo[1] *= f; uo[2] *= f;
-        }
-        const R uo2 = uo[0] * uo[0] + uo[1] * uo[1] + uo[2] * uo[2];
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
-          const R g = decode<R>(raw[i]);
-          const bool wall = beyond(i, ST_SOLID), inl = beyond(i, ST_INLET), outl = beyond(i, ST_OUTLET);
-          const R cui = R(cx(i)) * uw_in[0] + R(cy(i)) * uw_in[1] + (D == 3 ? R(cz(i)) * uw_in[2] : R(0));
-          const R cuo = R(cx(i)) * uo[0] + R(cy(i)) * uo[1] + (D == 3 ? R(cz(i)) * uo[2] : R(0));
-          const R vin = g + R(2.0 * wgt<Q>(i)) * rho_in * cui * invP0;
-          const R vout = -g + R(2.0 * wgt<Q>(i)) * ((R(a.outlet_P) + rho0 * (cuo * cuo * R(1.5) - uo2 * R(0.5))) * invP0 - R(1));
-          gh[i] = wall ? g : inl ? vin : outl ? vout : g;
-        }
-        if constexpr (FULL) {
-          if (a.lvl && (gw & linkmask)) {
-            // curved walls: interpolated bounce-back on the links cut inside the domain, the
-            // wall at the fraction q of the link to r - c_i; the second value of each link
-            // and the wall distances are again selected loads
-            const double l0 = a.lvl[n];
-#pragma unroll
-            for (int i = 0; i < Q; ++i) {
-              const int io = Q - 1 - i;
-              if (i == io) continue;
-              const bool cut = ((gw >> i) & 1) && !beyond(i, ST_SOLID) && !beyond(i, ST_INLET) && !beyond(i, ST_OUTLET);
-              const double ls = a.lvl[cut ? source(i) : un];
-              const R qf = cut ? (R)(l0 / (l0 - ls)) : R(0.5);
-              const bool near = qf < R(0.5);
-              // r + c_i is a fluid node of the domain
-              const bool ahead = !((gw >> io) & 1) && !beyond(io, ST_SOLID) && !beyond(io, ST_INLET) && !beyond(io, ST_OUTLET);
-              const unsigned e = near ? (unsigned)io * (unsigned)N + (ahead ? source(io) : un) : (unsigned)i * (unsigned)N + un;
-              const R g2 = decode<R>(ldg64(pin, e));
-              const R gopp = gh[i];
-              const R h = fdiv(R(1), R(2) * qf);
-              const R vnear = ahead ? lerp(g2, gopp, R(2) * qf) : gopp;
-              const R vfar = gopp * h + (R(1) - h) * g2;
-              gh[i] = cut ? (near ? vnear : vfar) : gopp;
-            }
-          }
-        }
-      }
-
-      // ---------------------------------------------------------------- moments (Eq. 7b)
-      R sg = R(0), mx = R(0), my = R(0), mz = R(0);
-#pragma unroll
-      for (int i = 0; i < Q; ++i) {
-        sg += gh[i];
-        if (cx(i)) mx += R(cx(i)) * gh[i];
-        if (cy(i)) my += R(cy(i)) * gh[i];
-        if (D == 3 && cz(i)) mz += R(cz(i)) * gh[i];
-      }
-      const R P0 = R(a.P0);
-      const R mom = R(3) * P0 * irho0;           // rho u = P0 sum c ghat / cs2
-      const R u[3] = {mx * mom, my * mom, D == 3 ? mz * mom : R(0)};
-      if constexpr (INTER) __builtin_amdgcn_s_setprio(0);
-
-      // ---------------------------------------------------------------- scalar stencils
-      // One pass per axis: the five stencil values of every scalar (ghost rules at walls,
-      // inlet, outlet), density at +-1 for grad rho and the diffusion coefficients, the
-      // centred diffusion fluxes and the WENO3 advective derivative.
-      R gradrho[3] = {R(0), R(0), R(0)};
-      R Lam = R(0);
-      R adv[NSV];
-#pragma unroll
-      for (int k = 0; k < NSV; ++k) adv[k] = R(0);
-      if constexpr (NS > 0) {
-        const R rhoD0 = rho0 * viscosity_irho(a.th, irho0) * a.th.inv_Pr;
-        const R rhoD_in = rho_in * viscosity(a.th, rho_in) * a.th.inv_Pr;
-        // cells whose +-2 stencil touches no face and no solid take the plain path
-        bool interior = gw == GW(0);
-#pragma unroll
-        for (int d = 0; d < D; ++d)
-          interior = interior && code[d][0] < 0 && code[d][1] < 0 && code[d][3] < 0 && code[d][4] < 0;
-        auto stencils = [&](auto fast_tag) {
-          constexpr bool FAST = decltype(fast_tag)::value;
-#pragma unroll
-          for (int d = 0; d < D; ++d) {
-            const int sp1 = FAST ? ST_FLUID : status(d, 1), sm1 = FAST ? ST_FLUID : status(d, -1);
-            const int sp2 = FAST ? ST_FLUID : status(d, 2), sm2 = FAST ? ST_FLUID : status(d, -2);
-            const unsigned mp1 = un + (unsigned)off[d][3], mm1 = un + (unsigned)off[d][1];
-            const unsigned mp2 = un + (unsigned)off[d][4], mm2 = un + (unsigned)off[d][0];
-            const R ud = u[d];
-            const bool up = ud >= R(0);
-            // FAST: vp1 holds the downwind neighbour and vm1 the upwind one (addresses
-            // chosen once per axis instead of values per scalar); diffusion and density are
-            // symmetric in the two, grad rho takes the sign back
-            const unsigned mdw = up ? mp1 : mm1, muw = up ? mm1 : mp1;
-            R vp1[NSV], vm1[NSV], fp2[NSV], fm2[NSV];
-            // general path: the four neighbours of every scalar by unconditional loads, a
-            // point that is not a fluid node replaced by the cell itself, so that they are all
-            // in flight together (loads inside branches waited for one another)
-            const unsigned ip1 = sp1 == ST_FLUID ? mp1 : un, im1 = sm1 == ST_FLUID ? mm1 : un;
-            const unsigned ip2 = sp1 == ST_FLUID && sp2 == ST_FLUID ? mp2 : un;
-            const unsigned im2 = sm1 == ST_FLUID && sm2 == ST_FLUID ? mm2 : un;
-#pragma unroll
-            for (int q = 0; q < NS; ++q) {
-              const Sc *sq = sin_ + (size_t)q * N;
-              if (FAST) {
-                vp1[q] = (R)bld<Sc>(slice(sq), mdw);
-                vm1[q] = (R)bld<Sc>(slice(sq), muw);
-              } else {
-                vp1[q] = (R)bld<Sc>(slice(sq), ip1);
-                vm1[q] = (R)bld<Sc>(slice(sq), im1);
-                if (!EXTRACT) {
-                  fp2[q] = (R)bld<Sc>(slice(sq), ip2);
-                  fm2[q] = (R)bld<Sc>(slice(sq), im2);
-                }
-                if (sp1 == ST_INLET) vp1[q] = phin[q];
-                if (sm1 == ST_INLET) vm1[q] = phin[q];
-              }
-            }
-            // curved walls: mirror images of solid cells at -1 / +1 (c1), of the stencil
-            // points at -2 / +2 behind them (c2, image at p2 from the cell) and of a solid
-            // cell at -2 / +2 behind a fluid neighbour (c3, weight w3 from that neighbour)
-            bool c1m = false, c1p = false, c2m = false, c2p = false, c3m = false, c3p = false;
-            R w1m = R(0), w1p = R(0), p2m = R(0), p2p = R(0), w3m = R(0), w3p = R(0);
-            if (FULL && !FAST && a.lvl) {
-              const double l0 = a.lvl[n];
-              if (sm1 == ST_SOLID && code[d][1] < 0 && sp1 == ST_FLUID) {
-                const R qw = (R)(l0 / (l0 - a.lvl[mm1]));
-                c1m = true;
-                w1m = image_weight(R(1) - R(2) * qw);
-                p2m = R(2) - R(2) * qw;
-                c2m = p2m <= R(1) || sp2 == ST_FLUID;
-              } else if (sm1 == ST_FLUID && sm2 == ST_SOLID && code[d][0] < 0) {
-                const double l1 = a.lvl[mm1];
-                c3m = true;
-                w3m = image_weight(R(1) - R(2) * (R)(l1 / (l1 - a.lvl[mm2])));
-              }
-              if (sp1 == ST_SOLID && code[d][3] < 0 && sm1 == ST_FLUID) {
-                const R qw = (R)(l0 / (l0 - a.lvl[mp1]));
-                c1p = true;
-                w1p = image_weight(R(1) - R(2) * qw);
-                p2p = R(2) - R(2) * qw;
-                c2p = p2p <= R(1) || sm2 == ST_FLUID;
-              } else if (sp1 == ST_FLUID && sp2 == ST_SOLID && code[d][4] < 0) {
-                const double l1 = a.lvl[mp1];
-                c3p = true;
-                w3p = image_weight(R(1) - R(2) * (R)(l1 / (l1 - a.lvl[mp2])));
-              }
-#pragma unroll
-              for (int q = 0; q < NS; ++q) {
-                const R am = vm1[q], ap = vp1[q];
-                if (c1m) vm1[q] = lerp(phi0[q], ap, w1m);
-                if (c1p) vp1[q] = lerp(phi0[q], am, w1p);
-              }
-            }
-            // density at +-1 and diffusion through the two faces
-            R rp = rho0, rm = rho0;
-            if (FAST || sp1 == ST_FLUID) rp = density<NS, R>(a.th, vp1, pim);
-            else if (sp1 == ST_INLET) rp = rho_in;
-            else if (c1p) rp = density<NS, R>(a.th, vp1, pim);
-            if (FAST || sm1 == ST_FLUID) rm = density<NS, R>(a.th, vm1, pim);
-            else if (sm1 == ST_INLET) rm = rho_in;
-            else if (c1m) rm = density<NS, R>(a.th, vm1, pim);
-            gradrho[d] = R(0.5) * (rp - rm);
-            if (FAST && !up) gradrho[d] = -gradrho[d];
-            // face coefficients: arithmetic mean of rho D (uniform when rho nu is constant)
-            R cfp, cfm;
-            if (FAST) {
-              cfp = a.th.const_mu ? rhoD0 : R(0.5) * (rhoD0 + rp * viscosity(a.th, rp) * a.th.inv_Pr);
-              cfm = a.th.const_mu ? rhoD0 : R(0.5) * (rhoD0 + rm * viscosity(a.th, rm) * a.th.inv_Pr);
-            } else {
-              const bool fp = sp1 == ST_FLUID || sp1 == ST_INLET, fm = sm1 == ST_FLUID || sm1 == ST_INLET;
-              cfp = fp ? R(0.5) * (rhoD0 + (sp1 == ST_INLET ? rhoD_in : rp * viscosity(a.th, rp) * a.th.inv_Pr)) : R(0);
-              cfm = fm ? R(0.5) * (rhoD0 + (sm1 == ST_INLET ? rhoD_in : rm * viscosity(a.th, rm) * a.th.inv_Pr)) : R(0);
-            }
-            const bool mixed = FULL && NS == 6 && a.mx.on;   // diffusion done before the pull
-            if (!mixed) {
-              // differences first: a sum of neighbours minus 2D phi0 would round with a
-              // bias near binade boundaries (values near 1 and 4) in FP32
-#pragma unroll
-              for (int q = 0; q < NS; ++q) R_s[q] += cfp * (vp1[q] - phi0[q]) + cfm * (vm1[q] - phi0[q]);
-            }
-            if (!EXTRACT) {
-              // WENO3 upwinded on the sign of u_d, written branch-free: with the upwind
-              // neighbours U1, U2 and the downwind neighbour D1,
-              // u_d dphi/dx_d = |u_d| (face(U1, 0, D1) - face(U2, U1, 0)).
-              const R au = fabs(ud);
-              const unsigned mfar = up ? mm2 : mp2;
-#pragma unroll
-              for (int q = 0; q < NS; ++q) {
-                const Sc *sq = sin_ + (size_t)q * N;
-                const R v0 = phi0[q];
-                R vU2;
-                if (FAST) {
-                  vU2 = (R)bld<Sc>(slice(sq), mfar);
-                } else {
-                  R vm2, vp2;
-                  if (sm1 == ST_FLUID) vm2 = sm2 == ST_FLUID ? fm2[q] : sm2 == ST_INLET ? phin[q] : vm1[q];
-                  else vm2 = sm1 == ST_SOLID ? vp1[q] : sm1 == ST_INLET ? phin[q] : v0;
-                  if (sp1 == ST_FLUID) vp2 = sp2 == ST_FLUID ? fp2[q] : sp2 == ST_INLET ? phin[q] : vp1[q];
-                  else vp2 = sp1 == ST_SOLID ? vm1[q] : sp1 == ST_INLET ? phin[q] : v0;
-                  if (c2m) vm2 = p2m <= R(1) ? lerp(v0, vp1[q], p2m) : lerp(vp1[q], fp2[q], p2m - R(1));
-                  else if (c3m) vm2 = lerp(vm1[q], v0, w3m);
-                  if (c2p) vp2 = p2p <= R(1) ? lerp(v0, vm1[q], p2p) : lerp(vm1[q], fm2[q], p2p - R(1));
-                  else if (c3p) vp2 = lerp(vp1[q], v0, w3p);
-                  vU2 = up ? vm2 : vp2;
-                }
-                const R vU1 = FAST || up ? vm1[q] : vp1[q];
-                const R vD1 = FAST || up ? vp1[q] : vm1[q];
-                adv[q] += au * weno3_diff(vU2, vU1, v0, vD1, a.eps[q]);
-              }
-            }
-          }
-        };
-        if (INTER || interior) stencils(std::true_type{});
-        else if constexpr (!INTER) stencils(std::false_type{});
-        const R Fr = a.th.F * irho0;
-#pragma unroll
-        for (int q = 0; q < NS; ++q) R_s[q] *= Fr;
-        if constexpr (FULL && NS == 6) {
-          if (a.mx.on) R_s[0] = fdiv(R_s[0], cp_c);
-        }
-        // chemistry (reaction over F) and Lambda (Eq. 3)
-        const R invF = a.th.invF;
-        if constexpr (NS == 2) {
-          const R r = a.th.B1 * fmax(phi0[1], R(0)) * hexp(-fdiv(a.th.Ta1, phi0[0]));
-          R_s[0] += a.th.heat1 * r * invF;
-          R_s[1] -= r * invF;
-          if (a.thermo) R_s[0] += a.kap * qn * phi0[0];   // pressure work
-          Lam = fdiv(R_s[0], phi0[0]);
-          if (a.thermo) Lam -= qn;                        // div u = Lambda - dln(pi)/dt
-        } else if constexpr (NS == 6) {
-          R conc[5];
-#pragma unroll
-          for (int q = 0; q < 5; ++q) conc[q] = rho0 * fmax(phi0[1 + q], R(0)) * a.th.inv_W[q];
-          const R T = phi0[0];
-          const R iT = fdiv(R(1), T);
-          const R q1 = a.th.B1 * hexp(-a.th.Ta1 * iT) * conc[0] * conc[1];
-          const R q2 = a.th.B2 * hexp(-a.th.Ta2 * iT) * conc[2] * hsqrt(conc[1]);
-          const R ir = irho0;
-          // molar rates per mass: sum over reactions of nu_k,r q_r, over rho
-          const R m0 = -q1 * ir, m1 = (R(-1.5) * q1 - R(0.5) * q2) * ir, m2 = (q1 - q2) * ir,
-                  m3 = q2 * ir, m4 = R(2) * q1 * ir;
-          R_s[1] += a.th.W[0] * m0 * invF;
-          R_s[2] += a.th.W[1] * m1 * invF;
-          R_s[3] += a.th.W[2] * m2 * invF;
-          R_s[4] += a.th.W[3] * m3 * invF;
-          R_s[5] += a.th.W[4] * m4 * invF;
-          R heat = -(a.th.h[0] * m0 + a.th.h[1] * m1 + a.th.h[2] * m2 + a.th.h[3] * m3 +
-                     a.th.h[4] * m4) * a.th.inv_cp;
-          if constexpr (FULL) {
-            if (a.mx.on) {
-              // full molar enthalpies h_k(T) and the mixture c_p
-              R hT[5];
-#pragma unroll
-              for (int q = 0; q < 5; ++q)
-                hT[q] = a.mx.hc[q] + a.th.W[q] * T * (a.mx.cpa[q] + R(0.5) * a.mx.cpb[q] * T);
-              heat = -fdiv(hT[0] * m0 + hT[1] * m1 + hT[2] * m2 + hT[3] * m3 + hT[4] * m4, cp_c);
-            }
-          }
-          R_s[0] += heat * invF;
-          if (a.thermo) R_s[0] += a.kap * qn * T;         // pressure work
-          // Lambda = R_T/T + W sum_k R_k/W_k (N2 by closure: R_N2 = -sum R_k)
-          R invW = a.th.inv_W[5], acc = R(0);
-#pragma unroll
-          for (int q = 0; q < 5; ++q) {
-            invW += phi0[1 + q] * a.th.dinv_W[q];
-            acc += R_s[1 + q] * a.th.dinv_W[q];
-          }
-          Lam = R_s[0] * iT + fdiv(acc, invW);
-          if (a.thermo) Lam -= qn;                        // div u = Lambda - dln(pi)/dt
-        }
-      }
-      // Eq. 7a: P_h = P0 (1 + sum ghat) + (dt/2) rho cs2 Lambda, formed in FP64 from the
-      // deviation sum (1 + sum ghat in the compute precision would round away the pressure
-      // fluctuation's last digits, and P0 in it is rounded too)
-      const R hLam = R(0.5) * rho0 * s * Lam;
-      const double Ph = a.P0d * (1.0 + (double)sg) + (double)hLam;
-
-      if (EXTRACT) {
-        if (a.f_P) a.f_P[n] = Ph;
-        if (a.f_rho) a.f_rho[n] = (double)rho0;
-        if (a.f_u)
-#pragma unroll
-          for (int d = 0; d < D; ++d) a.f_u[d * N + n] = (double)u[d];
-        if (a.f_scal)
-#pragma unroll
-          for (int k = 0; k < NS; ++k) a.f_scal[k * N + n] = (double)phi0[k];
-      } else {
-        // ------------------------------------------------------------ observables
-        // running mean and squared-deviation sums (Welford) of u and P_h - P0 at sampled
-        // levels; probe rows (u, P_h) at the probe cells
-        if (FULL && a.stats) {
-          const double x[4] = {(double)u[0], (double)u[1], (double)u[2], Ph - a.P0d};
-#pragma unroll
-          for (int j = 0; j <= D; ++j) {
-            const double xv = x[j == D ? 3 : j];
-            double *mp = a.stats + (size_t)j * N + n, *sp = a.stats + (size_t)(D + 1 + j) * N + n;
-            const double m0 = *mp;
-            const double m1 = m0 + (xv - m0) * a.inv_k;
-            *mp = m1;
-            *sp += (xv - m0) * (xv - m1);
-          }
-        }
-        if (FULL && a.probe_out) {
-          for (int j = 0; j < a.nprobe; ++j)
-            if (n == a.probe[j]) {
-#pragma unroll
-              for (int d = 0; d < D; ++d) a.probe_out[j * (D + 1) + d] = (double)u[d];
-              a.probe_out[j * (D + 1) + D] = Ph;
-            }
-        }
-        // ------------------------------------------------------------ scalar update
-        // one finiteness test for the step's outputs: a NaN or an infinity in any of
-        // them makes the sum non-finite (the finite values are far below overflow)
-        R chk = R(0);
-        R phi1[NSV];
-        phi1[0] = R(0);
-#pragma unroll
-        for (int q = 0; q < NS; ++q) {
-          const R nv = phi0[q] + (R_s[q] - adv[q]);
-          chk += nv;
-          // streaming stores where the grid exceeds the Infinity Cache (reacting box
-          // 0.857 -> 0.853 ms, with mixture transport 1.194 -> 1.186 ms); smaller grids
-          // keep the scalars in the cache for the next step's stencils.  The plain
-          // instances decide at compile time (the cached-pull ones are the large-grid
-          // ones; a run-time test there cost the 2-D chamber 2 %), the FULL ones at run time
-          if (PULLC || (FULL && a.big)) bst<Sc, 2>(slice(sout + (size_t)q * N), un, (Sc)nv);
-          else bst<Sc>(slice(sout + (size_t)q * N), un, (Sc)nv);
-          phi1[q] = (R)(Sc)nv;
-        }
-        if (a.thermo) red[8] = w_over_T<NS>(a.th, phi1, a.inv_T_ref_d);
-        // ------------------------------------------------------------ collision
-        const R r = a.th.rho_ref * irho0;               // P0/(rho cs2)
-        const R uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
-        const R ugr = u[0] * gradrho[0] + u[1] * gradrho[1] + u[2] * gradrho[2];
-        const R rsL = rho0 * s * Lam;
-        // Eq. 2: Xi_i = cs2 (f_eq/rho - w)(c - u).grad rho + w rho cs2 Lambda, formed once
-        // per population and kept for the post-collision form (Eq. 8), here already over
-        // 2 rho cs2 (the factor of Eq. 13) and less w_i Es (below).  Opposite velocities
-        // share c.u and c.grad rho up to sign: with a = c.u, b = c.grad rho,
-        // f_eq/rho - w = w (3a + 4.5a^2 - 1.5u.u), so each pair needs one square and the two
-        // signs of the odd parts.
-        R Xh[NS >= 2 ? Q : 1];
-        R e[Q];
-        // sum_i Xi_i = cs2 (rho Lambda + u . grad rho) (the moments of Eq. 2)
-        const R Xs = NS >= 2 ? s * (rho0 * Lam + ugr) : R(0);
-        // Es = sum_i of the pre-conditioned populations minus the weights (Eq. 13), from the
-        // moments: r sum ghat + sum Xi / (2 rho cs2); d = f~ - w = e - w Es has zero sum
-        const R Es = NS >= 2 ? r * sg + Xs * (R(1.5) * irho0) : sg;
-        if constexpr (NS >= 2) {
-          const R k1 = R(0.5) * irho0;                   // cs2 / (2 rho cs2)
-          const R k0 = R(0.5) * Lam - Es;                // rho cs2 Lambda / (2 rho cs2) - Es
-          const R e0 = R(-1.5) * uu;
-#pragma unroll
-          for (int i = 0; i < Q / 2; ++i) {
-            const int o = Q - 1 - i;
-            R a0 = R(0), b0 = R(0);
-            if (cx(i)) { a0 += R(cx(i)) * u[0]; b0 += R(cx(i)) * gradrho[0]; }
-            if (cy(i)) { a0 += R(cy(i)) * u[1]; b0 += R(cy(i)) * gradrho[1]; }
-            if (D == 3 && cz(i)) { a0 += R(cz(i)) * u[2]; b0 += R(cz(i)) * gradrho[2]; }
-            const R ev = R(4.5) * a0 * a0 + e0, od = R(3) * a0;
-            const R wk1 = R(wgt<Q>(i)) * k1, wk0 = R(wgt<Q>(i)) * k0;
-            Xh[i] = wk1 * ((ev + od) * (b0 - ugr)) + wk0;
-            Xh[o] = wk1 * ((ev - od) * (-b0 - ugr)) + wk0;
-          }
-          constexpr int c0 = Q / 2;
-          Xh[c0] = R(wgt<Q>(c0)) * (k1 * (e0 * -ugr) + k0);
-        }
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
-          if constexpr (NS >= 2) e[i] = r * gh[i] + Xh[i];          // d = f~ - w (Eq. 13)
-          else e[i] = gh[i] - R(wgt<Q>(i)) * Es;                     // rho = rho_ref, Xi = 0
-        }
-        R nu = viscosity_irho(a.th, irho0);
-        if constexpr (FULL && NS == 6) {
-          if (a.mx.on) nu = mu_c * irho0;
-        }
-        Rates<R> rt;
-        rt.tau0 = nu * R(3) + R(0.5);                    // nu / cs2 + 1/2
-        rt.smag18 = a.smag18;
-        rt.wb = a.wb;
-        rt.wh = a.wh;
-        rt.gal = a.gal != 0;
-        rt.p4 = a.p4 != 0;
-        const R hP0 = R(0.5) * a.invP0;
-        const R base = sg + Xs * hP0;                    // (1/r) m0 - 1
-        const R invr = rho0 * a.invP0 * s;              // rho/rho_ref = rho cs2/P0
-        const R baseE = NS >= 2 ? base + Es * invr : base;   // with the w_i Es taken from Xh
-        if constexpr (COLL != COLL_BGK) {
-          if constexpr (Q == 9) collide_d2q9(e, u[0], u[1], rt);
-          else collide_d3q27<R, COLL == COLL_CUM1>(e, u[0], u[1], u[2], rt);
-#pragma unroll
-          for (int i = 0; i < Q; ++i) {
-            R gs;
-            if constexpr (NS >= 2) gs = R(wgt<Q>(i)) * baseE + (e[i] + Xh[i]) * invr;   // Eq. 8
-            else gs = R(wgt<Q>(i)) * base + e[i];
-            bst<St, 2>(slice(pout + (size_t)i * N), un, encode<St>(gs));
-          }
-        } else {
-          // BGK in the pre-conditioned frame (Eq. 5 with the half-source split)
-          const R om = shear_rate(rt, pipi_of<Q, R>(e, u));
-          const R ph1 = sg + hLam * a.invP0;
-          const R kq = rho0 * s * a.invP0;
-#pragma unroll
-          for (int i = 0; i < Q; ++i) {
-            const R cu = R(cx(i)) * u[0] + R(cy(i)) * u[1] + (D == 3 ? R(cz(i)) * u[2] : R(0));
-            const R geq = R(wgt<Q>(i)) * (ph1 + kq * (R(3) * cu + R(4.5) * cu * cu - R(1.5) * uu));
-            R xh = R(0);
-            if constexpr (NS >= 2) xh = (Xh[i] + R(wgt<Q>(i)) * Es) * invr;
-            const R gp = gh[i] + xh;
-            bst<St, 2>(slice(pout + (size_t)i * N), un, encode<St>(gp - om * (gp - geq) + xh));
-          }
-        }
-        if (!isfinite(chk + sg + hLam + u[0] + u[1] + u[2])) atomicOr(a.flag, 1);
-      }
-
-      // ---------------------------------------------------------------- FP64 sums
-      // (cell values in the compute precision, accumulated in FP64)
-      red[0] = (double)rho0;
-      red[1] = Ph;
-      red[2] = (double)(rho0 * u[0]);
-      red[3] = (double)(rho0 * u[1]);
-      red[4] = (double)(rho0 * u[2]);
-      red[5] = (double)(R(0.5) * rho0 * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]));
-      red[6] = w_over_T<NS>(a.th, phi0, a.inv_T_ref_d);
-      if constexpr (NS >= 2) red[7] = (double)(rho0 * phi0[1]);
-    }
-  }
-  block_sums(red, a.partials + (size_t)(MODE == MODE_LIST ? (int)blockIdx.x : tile) * NSUM);
+  const int block = (int)blockIdx.x, nblocks = (int)gridDim.x;
+#include "lbm_step_cells.inc"
+  block_sums(red, a.partials + (size_t)tile * NSUM);
 }
 
+// D2Q9: a step split by kind of cell in one launch.  The first a.nlb blocks (a multiple of
+// 8, so that the tiles' blocks keep their XCDs) update the listed boundary cells, the others
+// the interior cells of their tile.  Both kinds need the same registers here, so one
+// kernel costs no occupancy, the long boundary chains start first and end under the interior
+// ones, and nothing waits for another stream's event.
+template <int PREC, int NS, bool LFULL, bool IFULL, int COLL, int IMODE, bool PULLC>
+__global__ __launch_bounds__(256) void split_kernel(KArgs<typename Prec<PREC>::R>) {
+  const auto &a = kernel_args<typename Prec<PREC>::R>();
+  double red[NSUM] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+  const int block = (int)blockIdx.x - a.nlb, ntiles = (int)gridDim.x - a.nlb;
+  int rec;
+  if (block < 0) {
+    rec = ntiles + step_cells<9, PREC, NS, false, LFULL, COLL, MODE_LIST, false>(a, blockIdx.x, a.nlb, red);
+  } else {
+    rec = step_cells<9, PREC, NS, false, IFULL, COLL, IMODE, PULLC>(a, block, ntiles, red);
+  }
+  block_sums(red, a.partials + (size_t)rec * NSUM);
+}
 
 // Deterministic reduction of the per-block records: stage 1 gives each of up to 256
 // blocks a contiguous range of records, stage 2 sums the stage-1 records in one block.
