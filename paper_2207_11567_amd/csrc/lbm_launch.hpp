@@ -63,17 +63,39 @@ template <int Q, int PREC, int NS, bool FULL, int MODE>
 hipError_t launch_step(const StepArgs &a, int nblocks, hipStream_t st) {
   using R = typename Prec<PREC>::R;
   switch (collision_instance<Q, PREC>(a)) {
-    case COLL_CUM1:
+    case COLL_CUM1: {
+      constexpr bool free = MODE == MODE_FREE || MODE == MODE_FREE_LIN;
+      constexpr bool inter = MODE == MODE_INTERIOR || MODE == MODE_INTERIOR_LIN;
+      // FP32 steps without boundaries: dynamic LDS leaves five blocks a CU instead of eight.
+      // More waves in flight than the memory side needs cost it locality (HIT FP32, us per step
+      // at 8 / 7 / 6 / 5 / 4 blocks: 256^3 667 / 660 / 646 / 643 / 643, 128^3 87.9 / 87.1 / 85.2 /
+      // 84.9 / 85.2; passive 128^3 92.0 / 91.9 / 90.2 / 90.8 / 90.6).  FP16 storage, bound by
+      // issue, wants them all (377 / 380 / 396 / 422 / 425), FP64 holds six by its registers.
+      // Grids of a few passes gain nothing and a single pass loses (passive 64^3 12.8 / 14.1).
+      const unsigned lds = Q == 27 && PREC == 1 && free && nblocks >= 4096 ? 14000 : 0;
+      // SEG by kind of step, not by size, so that a grid rounds as its copies side by side do
+      constexpr bool seg = Q == 27 && ((PREC != 0 && NS == 6 && inter) || (PREC == 2 && free)) && !FULL;
       // the plain production instances also come with cached pull loads (large grids)
-      if constexpr (!FULL && MODE != MODE_LIST)
-        if (a.pull_cached) {
-          hipLaunchKernelGGL((step_kernel<Q, PREC, NS, false, false, COLL_CUM1, MODE, true>), dim3(nblocks), dim3(256),
-                             0, st, to_kargs<R>(a));
+      if constexpr (!FULL && MODE != MODE_LIST) {
+        if (seg && !a.lvl) {
+          if (a.pull_cached)
+            hipLaunchKernelGGL((step_kernel<Q, PREC, NS, false, false, COLL_CUM1, MODE, true, seg>), dim3(nblocks),
+                               dim3(256), 0, st, to_kargs<R>(a));
+          else
+            hipLaunchKernelGGL((step_kernel<Q, PREC, NS, false, false, COLL_CUM1, MODE, false, seg>), dim3(nblocks),
+                               dim3(256), 0, st, to_kargs<R>(a));
           break;
         }
-      hipLaunchKernelGGL((step_kernel<Q, PREC, NS, false, FULL, COLL_CUM1, MODE>), dim3(nblocks), dim3(256), 0, st,
+        if (a.pull_cached) {
+          hipLaunchKernelGGL((step_kernel<Q, PREC, NS, false, false, COLL_CUM1, MODE, true>), dim3(nblocks), dim3(256),
+                             lds, st, to_kargs<R>(a));
+          break;
+        }
+      }
+      hipLaunchKernelGGL((step_kernel<Q, PREC, NS, false, FULL, COLL_CUM1, MODE>), dim3(nblocks), dim3(256), lds, st,
                          to_kargs<R>(a));
       break;
+    }
     case COLL_CUM:
       if constexpr (Q == 27)
         hipLaunchKernelGGL((step_kernel<Q, PREC, NS, false, FULL, COLL_CUM, MODE>), dim3(nblocks), dim3(256), 0, st,
@@ -112,9 +134,9 @@ hipError_t launch_one(int kind, const StepArgs &a, int nblocks, hipStream_t st, 
     case LAUNCH_STEP:
       if (full) return launch_step<Q, PREC, NS, true, MODE_ALL>(a, nblocks, st);
       // no boundary anywhere: no boundary code (us per step, all-cell / free instance: vortex
-      // 128^2 FP64 6.0 / 4.8, HIT 100^3 FP16 storage 29.3 / 28.3, 128^3 FP32 89.2 / 88.0).  FP32
-      // populations beyond the Infinity Cache measured the other way: 256^3 655 / 666
-      if (without_boundaries(a) && !(PREC == 1 && a.pull_cached))
+      // 128^2 FP64 6.0 / 4.8, HIT 100^3 FP16 storage 29.3 / 28.3, 128^3 FP32 90.8 / 84.9)
+      // (not the FP64 step with a scalar: 48^3 12.3 / 12.9, 128^3 equal)
+      if (without_boundaries(a) && !(PREC == 0 && NS == 1))
         return a.band_rows ? launch_step<Q, PREC, NS, false, MODE_FREE>(a, nblocks, st)
                            : launch_step<Q, PREC, NS, false, MODE_FREE_LIN>(a, nblocks, st);
       return launch_step<Q, PREC, NS, false, MODE_ALL>(a, nblocks, st);

@@ -423,14 +423,26 @@ constexpr int step_waves_per_eu() {
   }
   return PREC != 0 && NS == 6 ? 4 : 1;
 }
-template <int Q, int PREC, int NS, bool EXTRACT, bool FULL, int COLL, int MODE, bool PULLC = false>
+// SEG: the arguments are read where the launch put them, through step_cells, instead of as the
+// kernel's parameter; the same arithmetic, another register allocation (118 instead of 112
+// VGPRs, other places of the loads).  Measured per kind of step: faster for the interior cells of
+// the two-step step (reacting box 192x192x384 FP32 843 -> 827 us, FP16 storage 713 -> 681) and
+// for HIT 256^3 with FP16 storage (378 -> 365), slower beside the curved-wall list (cone
+// 128x128x256 298 -> 330: its waves no longer fit beside three interior ones).
+template <int Q, int PREC, int NS, bool EXTRACT, bool FULL, int COLL, int MODE, bool PULLC = false, bool SEG = false>
 __global__ __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(step_waves_per_eu<Q, PREC, NS, EXTRACT, FULL, COLL, MODE>())))
 void step_kernel(KArgs<typename Prec<PREC>::R> a) {
   double red[NSUM] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-  const int block = (int)blockIdx.x, nblocks = (int)gridDim.x;
+  if constexpr (SEG) {
+    const auto &ka = kernel_args<typename Prec<PREC>::R>();
+    const int tile = step_cells<Q, PREC, NS, EXTRACT, FULL, COLL, MODE, PULLC>(ka, blockIdx.x, gridDim.x, red);
+    block_sums(red, ka.partials + (size_t)tile * NSUM);
+  } else {
+    const int block = (int)blockIdx.x, nblocks = (int)gridDim.x;
 #include "lbm_step_cells.inc"
-  block_sums(red, a.partials + (size_t)tile * NSUM);
+    block_sums(red, a.partials + (size_t)tile * NSUM);
+  }
 }
 
 // D2Q9: a step split by kind of cell in one launch.  The first a.nlb blocks (a multiple of
