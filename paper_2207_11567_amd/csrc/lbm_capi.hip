@@ -28,6 +28,7 @@ struct lbm_solver {
   int Q, NS, D, prec, nblocks;
   int *flag;
   double *sums;
+  double *host;       // pinned host copy of the work buffer's head (flag, sums, thermo)
   double *partials;   // block records of lbm_step: [nblocks] tiles, then [list blocks]
   double *aux;        // block records of field extraction, flame surface and objective
   int *cells;         // linear indices of the boundary cells (the step's list half)
@@ -39,6 +40,7 @@ struct lbm_solver {
   hipEvent_t ev_fork, ev_join;
   bool side_ready;
   ~lbm_solver() {
+    if (host) (void)hipHostFree(host);
     if (side_ready) {
       (void)hipStreamSynchronize(side);
       (void)hipEventDestroy(ev_fork);
@@ -354,16 +356,44 @@ static hipError_t launch(const lbm_solver *s, int kind, const StepArgs &a, const
   return launch_d3q27(s->prec, s->NS, kind, a, s->nblocks, s->stream, Ph, u, scal);
 }
 
-static lbm_status check_flag(lbm_solver *s) {
+// Waits for the stream, whose last kernel has put the head into the host copy, and looks at
+// the divergence flag there.
+static lbm_status wait_and_check(lbm_solver *s) {
+  const hipError_t e = hipStreamSynchronize(s->stream);
+  if (e != hipSuccess) return hip_fail(s, e, "waiting for the stream");
   int f = 0;
-  hipError_t e = hipMemcpyAsync(&f, s->flag, sizeof(int), hipMemcpyDeviceToHost, s->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
-  if (e != hipSuccess) return hip_fail(s, e, "reading the divergence flag");
+  memcpy(&f, s->host, sizeof f);
   if (f & 1) {
     s->err = "a non-finite value appeared during a time step";
     return LBM_E_DIVERGED;
   }
   return LBM_OK;
+}
+
+static const double *head_of(const lbm_solver *s) { return (const double *)s->work; }
+
+static lbm_status wait_for_sums(lbm_solver *s, double *sums_host) {
+  const lbm_status st = wait_and_check(s);
+  if (sums_host && st != LBM_E_HIP) memcpy(sums_host, s->host + HEAD_SUMS, 8 * sizeof(double));
+  return st;
+}
+
+// Memory of the current device that a kernel of this solver may write directly.
+static bool local_memory(const void *p, size_t bytes) {
+  if (((uintptr_t)p | bytes) & 15) return false;
+  hipPointerAttribute_t at;
+  int dev = -1;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return at.type == hipMemoryTypeDevice && hipGetDevice(&dev) == hipSuccess && at.device == dev;
+}
+
+static lbm_status check_flag(lbm_solver *s) {
+  const hipError_t e = launch_publish(head_of(s), s->host, s->stream);
+  if (e != hipSuccess) return hip_fail(s, e, "reading the divergence flag");
+  return wait_and_check(s);
 }
 
 // The boundary cells of the split step, in increasing linear index: a non-zero geometry
@@ -388,6 +418,7 @@ static hipError_t build_cell_list(lbm_solver *s) {
   for (int z = 0; z < p.nz; ++z)
     for (int y = 0; y < p.ny; ++y) {
       const bool row = host_near_face(y, p.ny, a.face[2], a.face[3]) || host_near_face(z, p.nz, a.face[4], a.face[5]);
+      if (!row && !s->has_geom && a.face[0] < 0 && a.face[1] < 0) continue;     // all of it interior
       for (int x = 0; x < p.nx; ++x) {
         const long long n = x + (long long)p.nx * (y + (long long)p.ny * z);
         bool g = row || host_near_face(x, p.nx, a.face[0], a.face[1]);
@@ -603,8 +634,10 @@ lbm_status lbm_create(const lbm_params *p, void *stream, void *pop_a, void *pop_
   s->nprobe = 0;
   s->probe_cap = s->probe_rows = 0;
   s->geom = s->work + L.off_geom;
+  s->host = nullptr;
   s->scratch = scratch_on_current_device(s->scratch_err);   // the solver's device is the current one
-  hipError_t e = hipMemsetAsync(s->work, 0, 256, s->stream);
+  hipError_t e = hipHostMalloc((void **)&s->host, HEAD_WORDS * sizeof(double), hipHostMallocDefault);
+  if (e == hipSuccess) e = hipMemsetAsync(s->work, 0, 256, s->stream);
   if (e == hipSuccess) e = launch_set_thermo(s->thermo, 1.0, 0.0, 0.0, s->stream);
   if (e == hipSuccess) e = build_cell_list(s);
   if (e != hipSuccess) {
@@ -663,12 +696,9 @@ lbm_status lbm_init_fields(lbm_solver *s, const double *P_h, const double *u, co
   StepArgs a = make_args(s);
   a.pop_out = s->pop[s->cur];
   a.scal_out = s->scal[s->cur];
+  a.thermo = s->thermo;                 // reset there, with the divergence flag
   hipError_t e = launch(s, LAUNCH_INIT, a, P_h, u, scal);
   if (e != hipSuccess) return hip_fail(s, e, "init kernel");
-  e = launch_set_thermo(s->thermo, 1.0, 0.0, 0.0, s->stream);
-  if (e != hipSuccess) return hip_fail(s, e, "resetting the thermodynamic pressure");
-  e = hipMemsetAsync(s->flag, 0, sizeof(int), s->stream);
-  if (e != hipSuccess) return hip_fail(s, e, "clearing the divergence flag");
   s->initialized = true;
   return LBM_OK;
 }
@@ -740,13 +770,9 @@ lbm_status lbm_step_from(lbm_solver *s, const void *pops_in, const void *scal_in
 
 lbm_status lbm_step_sums(lbm_solver *s, double *sums_host) {
   if (!s) return LBM_E_INVALID;
-  hipError_t e = launch_finalize(s->partials, s->nrec, s->stage, s->sums, s->stream);
+  hipError_t e = launch_finalize(s->partials, s->nrec, s->stage, s->sums, s->stream, head_of(s), s->host);
   if (e != hipSuccess) return hip_fail(s, e, "finalize kernel");
-  if (sums_host) {
-    e = hipMemcpyAsync(sums_host, s->sums, 8 * sizeof(double), hipMemcpyDeviceToHost, s->stream);
-    if (e != hipSuccess) return hip_fail(s, e, "copying sums");
-  }
-  return check_flag(s);
+  return wait_for_sums(s, sums_host);
 }
 
 lbm_status lbm_fields(lbm_solver *s, double *P_h, double *rho, double *u, double *scal, double *sums_host) {
@@ -765,21 +791,26 @@ lbm_status lbm_fields(lbm_solver *s, double *P_h, double *rho, double *u, double
   a.partials = s->aux;                  // the step's own records stay for lbm_step_sums
   hipError_t e = launch(s, LAUNCH_EXTRACT, a);
   if (e != hipSuccess) return hip_fail(s, e, "field extraction kernel");
-  e = launch_finalize(s->aux, s->nblocks, s->stage, s->sums, s->stream);
+  e = launch_finalize(s->aux, s->nblocks, s->stage, s->sums, s->stream, head_of(s), s->host);
   if (e != hipSuccess) return hip_fail(s, e, "finalize kernel");
-  if (sums_host) {
-    e = hipMemcpyAsync(sums_host, s->sums, 8 * sizeof(double), hipMemcpyDeviceToHost, s->stream);
-    if (e != hipSuccess) return hip_fail(s, e, "copying sums");
-  }
-  return check_flag(s);
+  return wait_for_sums(s, sums_host);
 }
 
 lbm_status lbm_get_state(lbm_solver *s, void *pops_dst, void *scal_dst, int64_t *step) {
   if (!s) return LBM_E_INVALID;
   const size_t pb = (size_t)s->Q * s->N * pop_elem(s->prec), sb = (size_t)s->NS * s->N * scal_elem(s->prec);
   hipError_t e = hipSuccess;
+  const bool scal = scal_dst && sb;
+  if (pops_dst && local_memory(pops_dst, pb) && local_memory(s->pop[s->cur], pb) &&
+      (!scal || (local_memory(scal_dst, sb) && local_memory(s->scal[s->cur], sb)))) {
+    e = launch_copy_state(s->pop[s->cur], pops_dst, pb, s->scal[s->cur], scal_dst, scal ? sb : 0, head_of(s), s->host,
+                          s->stream);
+    if (e != hipSuccess) return hip_fail(s, e, "copying the state out");
+    if (step) *step = s->step;
+    return wait_and_check(s);
+  }
   if (pops_dst) e = hipMemcpyAsync(pops_dst, s->pop[s->cur], pb, hipMemcpyDeviceToDevice, s->stream);
-  if (e == hipSuccess && scal_dst && sb)
+  if (e == hipSuccess && scal)
     e = hipMemcpyAsync(scal_dst, s->scal[s->cur], sb, hipMemcpyDeviceToDevice, s->stream);
   if (e != hipSuccess) return hip_fail(s, e, "copying the state out");
   if (step) *step = s->step;
@@ -878,10 +909,10 @@ lbm_status lbm_flame_surface(lbm_solver *s, double T_u, double T_b, double *surf
   a.scal_in = s->scal[s->cur];
   a.partials = s->aux;
   hipError_t e = launch_surface(s->Q, s->prec, a, s->nblocks, s->stream, T_u, T_b);
-  if (e == hipSuccess) e = launch_finalize(s->aux, s->nblocks, s->stage, s->sums, s->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(surface_host, s->sums, sizeof(double), hipMemcpyDeviceToHost, s->stream);
+  if (e == hipSuccess) e = launch_finalize(s->aux, s->nblocks, s->stage, s->sums, s->stream, head_of(s), s->host);
   if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
   if (e != hipSuccess) return hip_fail(s, e, "flame surface");
+  *surface_host = s->host[HEAD_SUMS];
   return LBM_OK;
 }
 
@@ -953,9 +984,10 @@ lbm_status lbm_copy_probe(const void *src, void *dst, size_t bytes, int32_t mode
 
 lbm_status lbm_get_thermo_pressure(lbm_solver *s, double *pqk_host) {
   if (!s || !pqk_host) return LBM_E_INVALID;
-  hipError_t e = hipMemcpyAsync(pqk_host, s->thermo, 3 * sizeof(double), hipMemcpyDeviceToHost, s->stream);
+  hipError_t e = launch_publish(head_of(s), s->host, s->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
   if (e != hipSuccess) return hip_fail(s, e, "reading the thermodynamic pressure");
+  memcpy(pqk_host, s->host + (s->thermo - s->sums) + HEAD_SUMS, 3 * sizeof(double));
   return LBM_OK;
 }
 
@@ -1049,10 +1081,10 @@ lbm_status lbm_objective(lbm_solver *s, const void *state_pops, const void *stat
                                 nullptr, 0.0, nullptr, nullptr);
   if (e != hipSuccess) return hip_fail(s, e, "objective sums");
   double sums[8];
-  e = launch_finalize(s->aux, s->nblocks, s->stage, s->sums, s->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(sums, s->sums, sizeof sums, hipMemcpyDeviceToHost, s->stream);
+  e = launch_finalize(s->aux, s->nblocks, s->stage, s->sums, s->stream, head_of(s), s->host);
   if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
   if (e != hipSuccess) return hip_fail(s, e, "objective sums");
+  memcpy(sums, s->host + HEAD_SUMS, sizeof sums);
   const double mean_T = sums[1] / (double)s->N;
   if (J_host) *J_host = sums[0] + (s->NS ? sums[2] - sums[1] * mean_T : 0.0);
   if (adj_pop_out) {

@@ -35,12 +35,37 @@ hipError_t launch_geometry_levelset(int Q, const double *phi, void *geom, int nx
   return geometry(Q, phi, geom, nx, ny, nz, N, f, st);
 }
 
-hipError_t launch_finalize(const double *partials, int nblocks, double *stage, double *out, hipStream_t st,
-                           double *thermo) {
-  const int nb1 = nblocks < 256 ? nblocks : 256;
-  const int chunk = (nblocks + nb1 - 1) / nb1;
-  hipLaunchKernelGGL(finalize_stage, dim3(nb1), dim3(256), 0, st, partials, nblocks, chunk, stage, (double *)nullptr);
-  hipLaunchKernelGGL(finalize_stage, dim3(1), dim3(256), 0, st, (const double *)stage, nb1, nb1, out, thermo);
+hipError_t launch_finalize(const double *partials, int nrec, double *stage, double *out, hipStream_t st,
+                           const double *head, double *host) {
+  // one launch up to 4096 records; more in chunks of at least 512 (at most 256 of them) first
+  if (nrec > 4096) {
+    const int chunk = nrec > 512 * 256 ? (nrec + 255) / 256 : 512;
+    const int nb = (nrec + chunk - 1) / chunk;
+    hipLaunchKernelGGL(reduce_records, dim3(nb), dim3(1024), 0, st, partials, nrec, chunk, stage, (const double *)nullptr,
+                       (double *)nullptr);
+    partials = stage;
+    nrec = nb;
+  }
+  hipLaunchKernelGGL(reduce_records, dim3(1), dim3(1024), 0, st, partials, nrec, nrec, out, head, host);
+  return hipGetLastError();
+}
+
+hipError_t launch_publish(const double *head, double *host, hipStream_t st) {
+  hipLaunchKernelGGL(publish_kernel, dim3(1), dim3(64), 0, st, head, host);
+  return hipGetLastError();
+}
+
+hipError_t launch_copy_state(const void *a, void *da, size_t abytes, const void *b, void *db, size_t bbytes,
+                             const double *head, double *host, hipStream_t st) {
+  const size_t na = abytes / 16, nb = bbytes / 16, most = na > nb ? na : nb;
+  const size_t blocks = (most + 1023) / 1024;
+  const dim3 grid((unsigned)(blocks < 1 ? 1 : blocks > 16384 ? 16384 : blocks));
+  if (abytes + bbytes > ((size_t)128 << 20))      // source and destination exceed the Infinity Cache
+    hipLaunchKernelGGL(copy_state_kernel<true>, grid, dim3(256), 0, st, (const u32x4 *)a, (u32x4 *)da, na, (const u32x4 *)b,
+                       (u32x4 *)db, nb, head, host);
+  else
+    hipLaunchKernelGGL(copy_state_kernel<false>, grid, dim3(256), 0, st, (const u32x4 *)a, (u32x4 *)da, na, (const u32x4 *)b,
+                       (u32x4 *)db, nb, head, host);
   return hipGetLastError();
 }
 

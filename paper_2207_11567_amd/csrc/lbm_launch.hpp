@@ -30,10 +30,14 @@ hipError_t launch_geometry_levelset(int Q, const double *phi, void *geom, int nx
 // 3: reverse of the initialisation (p0 lamA, p1 lamT, u0, gu out, p3 grad T out).
 hipError_t launch_adjoint(int prec, int ns, int kind, const StepArgs &sa, int nblocks, hipStream_t st, const void *p0,
                           const void *p1, void *p2, void *p3, void *p4, double mean_T, const double *u0, double *gu);
-// Sums of the per-block records into out[NSUM]; with thermo (closed domain) also the
-// thermodynamic pressure of the next level.
-hipError_t launch_finalize(const double *partials, int nblocks, double *stage, double *out, hipStream_t st,
-                           double *thermo = nullptr);
+// Sums of the per-block records into out[NSUM] and, with a host copy of the work buffer's
+// head (out is then its sums), the head to the host.
+hipError_t launch_finalize(const double *partials, int nrec, double *stage, double *out, hipStream_t st,
+                           const double *head = nullptr, double *host = nullptr);
+hipError_t launch_publish(const double *head, double *host, hipStream_t st);
+// Two arrays (bytes multiples of 16, 16-byte aligned) copied in one launch, and the head.
+hipError_t launch_copy_state(const void *a, void *da, size_t abytes, const void *b, void *db, size_t bbytes,
+                             const double *head, double *host, hipStream_t st);
 hipError_t launch_set_thermo(double *thermo, double pi, double q, double K, hipStream_t st);
 // Closed domain: (pi, q, K) of the next level from the step's nrec block records.
 hipError_t launch_thermo(const double *partials, int nrec, double *thermo, hipStream_t st);
@@ -176,7 +180,7 @@ hipError_t launch_one(int kind, const StepArgs &a, int nblocks, hipStream_t st, 
       break;
     default:
       hipLaunchKernelGGL((init_kernel<Q, PREC, NS>), dim3(nblocks), dim3(256), 0, st, to_kargs<double>(a), Ph, u,
-                         scal);
+                         scal, const_cast<double *>(a.thermo));
   }
   return hipGetLastError();
 }

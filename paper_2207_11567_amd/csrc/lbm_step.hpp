@@ -464,50 +464,82 @@ __global__ __launch_bounds__(256) void split_kernel(KArgs<typename Prec<PREC>::R
   block_sums(red, a.partials + (size_t)rec * NSUM);
 }
 
-// Deterministic reduction of the per-block records: stage 1 gives each of up to 256
-// blocks a contiguous range of records, stage 2 sums the stage-1 records in one block.
-// The order of every addition is fixed by the launch shape, so results are bitwise
-// repeatable.  Given thermo (closed domain, stage 2 only), the final sums also advance
-// (pi, q, K): K = pi sum W/T at the first step, pi' = K / sum W/T of the updated
-// scalars (the total mass is held), q' = (pi' - pi)/pi.
-static __global__ __launch_bounds__(256) void finalize_stage(const double *in, int nrec, int chunk, double *out,
-                                                             double *thermo) {
-  __shared__ double sh[NSUM][256];
-  const int b0 = blockIdx.x * chunk;
-  const int b1 = min(nrec, b0 + chunk);
-  double acc[NSUM];
-#pragma unroll
-  for (int k = 0; k < NSUM; ++k) acc[k] = 0.0;
-  for (int b = b0 + (int)threadIdx.x; b < b1; b += 256)
-#pragma unroll
-    for (int k = 0; k < NSUM; ++k) acc[k] += in[(size_t)b * NSUM + k];
-#pragma unroll
-  for (int k = 0; k < NSUM; ++k) sh[k][threadIdx.x] = acc[k];
+// The first bytes of the work buffer (divergence flag at 0, final sums at 64, thermodynamic
+// pressure at 192): 32 doubles that the synchronising calls hand to the host, written by a
+// kernel of the call straight into the solver's pinned host copy (a device-to-host copy of
+// each piece cost a launch and a staging wait of its own).
+constexpr int HEAD_WORDS = 32, HEAD_SUMS = 8;
+
+// Deterministic reduction of block records, nrec x NSUM doubles read as one contiguous run:
+// thread t of the first 1017 (a multiple of NSUM) adds elements t, t + 1017, ..., all of one
+// counter, then wave k combines counter k.  Each block sums `chunk` records; the order of
+// every addition is fixed by the launch shape, so results are bitwise repeatable.  With a
+// host copy (one block, out in the work buffer's head) the whole head goes there too.
+// Records read as rows of NSUM by 256 threads and summed in two launches took 9 us for the
+// 1024..4900 records of the 2-D workloads, this one 4 to 6.
+static __global__ __launch_bounds__(1024) void reduce_records(const double *in, int nrec, int chunk, double *out,
+                                                              const double *head, double *host) {
+  constexpr int USED = 1024 / NSUM * NSUM, GROUPS = USED / NSUM;
+  __shared__ double sh[USED];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const long long b0 = (long long)blockIdx.x * chunk;
+  const int count = (int)min((long long)chunk, nrec - b0) * NSUM;
+  const double *rec = in + b0 * NSUM;
+  if (t < USED) {
+    double acc = 0.0;
+#pragma unroll 8
+    for (int e = t; e < count; e += USED) acc += rec[e];
+    sh[t] = acc;
+  }
   __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off)
+  if (w < NSUM) {
+    double acc = 0.0;
+    for (int j = lane; j < GROUPS; j += 64) acc += sh[j * NSUM + w];
+    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+    if (lane == 0) {
+      out[(size_t)blockIdx.x * NSUM + w] = acc;
+      if (host) host[HEAD_SUMS + w] = acc;
+    }
+  }
+  if (host && t < HEAD_WORDS && (t < HEAD_SUMS || t >= HEAD_SUMS + NSUM)) host[t] = head[t];
+}
+
+// The head alone, for calls without a kernel that could pass it on.
+static __global__ void publish_kernel(const double *head, double *host) {
+  if (threadIdx.x < HEAD_WORDS) host[threadIdx.x] = head[threadIdx.x];
+}
+
+// State copy: two arrays of 16-byte words in one launch, four words in flight per thread, and
+// the head for the host.  Streaming where the copy exceeds the Infinity Cache (get_state of
+// the 192x192x384 FP32 reacting box 0.78 ms as the runtime's copies, 4.7 TB/s).
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+template <bool STREAM>
+__device__ __forceinline__ void copy_words(const u32x4 *src, u32x4 *dst, size_t n, size_t i, size_t stride) {
+  for (; i + 3 * stride < n; i += 4 * stride) {
+    u32x4 v[4];
 #pragma unroll
-      for (int k = 0; k < NSUM; ++k) sh[k][threadIdx.x] += sh[k][threadIdx.x + off];
-    __syncthreads();
+    for (int j = 0; j < 4; ++j) v[j] = STREAM ? __builtin_nontemporal_load(src + i + j * stride) : src[i + j * stride];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (STREAM) __builtin_nontemporal_store(v[j], dst + i + j * stride);
+      else dst[i + j * stride] = v[j];
   }
-  if (threadIdx.x < NSUM) out[(size_t)blockIdx.x * NSUM + threadIdx.x] = sh[threadIdx.x][0];
-  if (thermo && threadIdx.x == 0) {
-    const double pi = thermo[0];
-    double K = thermo[2];
-    if (!(K > 0.0)) K = pi * sh[6][0];
-    const double pn = K / sh[8][0];
-    thermo[0] = pn;
-    thermo[1] = (pn - pi) / pi;
-    thermo[2] = K;
-  }
+  for (; i < n; i += stride) dst[i] = src[i];
+}
+template <bool STREAM>
+__global__ __launch_bounds__(256) void copy_state_kernel(const u32x4 *a, u32x4 *da, size_t na, const u32x4 *b, u32x4 *db,
+                                                         size_t nb, const double *head, double *host) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x, stride = (size_t)gridDim.x * 256;
+  if (i < HEAD_WORDS) host[i] = head[i];
+  copy_words<STREAM>(a, da, na, i, stride);
+  copy_words<STREAM>(b, db, nb, i, stride);
 }
 
 // Closed domain, after every step: (pi, q, K) advanced from the two sums it needs, sum W/T
 // at level n and of the updated scalars (record entries 6 and 8), in one block of 1024
 // threads: thread t adds records t, t + 1024, ..., then the lanes of each wave by a
 // butterfly (lane 0's value kept) and the 16 waves in order.  A fixed order of additions,
-// so the result is bitwise repeatable; one short kernel instead of the two stages of
-// finalize_stage over all NSUM entries (chamber 2500x500: 9.4 us of dependent latency).
+// so the result is bitwise repeatable; one short kernel over two of the NSUM entries.
 static __global__ __launch_bounds__(1024) void thermo_kernel(const double *rec, int nrec, double *thermo) {
   __shared__ double part[2][16];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
@@ -645,15 +677,36 @@ __global__ __launch_bounds__(256) void geometry_kernel(const Src *solid, void *g
   ((GW *)geom)[n] = w;
 }
 
-// Equilibrium initialisation (Eq. 6) from FP64 fields; populations stored as deviations.
+// FP64 value to the storage precision, round to nearest even.  FP16 goes through FP32
+// rounded to odd (the inexact bit kept in the last place), which the second rounding turns
+// into the correct FP16: 8 instructions; the compiler's own conversion takes about 30.
+template <class St> __device__ __forceinline__ St store_cast(double x) {
+  if constexpr (sizeof(St) == 2) {
+    const float f = (float)x;
+    unsigned b = __builtin_bit_cast(unsigned, f);
+    const double r = (double)f;
+    if (r != x) b = (b - (fabs(r) > fabs(x) ? 1u : 0u)) | 1u;
+    return (St)__builtin_bit_cast(float, b);
+  } else {
+    return (St)x;
+  }
+}
+
+// Equilibrium initialisation (Eq. 6) from FP64 fields; populations stored as deviations.  The
+// first thread also resets the thermodynamic pressure and the divergence flag.
 template <int Q, int PREC, int NS>
 __global__ __launch_bounds__(256) void init_kernel(KArgs<double> a, const double *Ph, const double *u,
-                                                   const double *scal) {
+                                                   const double *scal, double *thermo) {
   using P = Prec<PREC>;
   using St = typename P::St;
   using Sc = typename P::Sc;
   constexpr int D = Lat<Q>::D;
   constexpr int NSV = NS > 0 ? NS : 1;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    thermo[0] = 1.0;
+    thermo[1] = thermo[2] = 0.0;
+    *a.flag = 0;
+  }
   const long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   const long long N = a.N;
   if (n >= N) return;
@@ -671,7 +724,7 @@ __global__ __launch_bounds__(256) void init_kernel(KArgs<double> a, const double
   for (int i = 0; i < Q; ++i) {
     const double cu = cx(i) * ux + cy(i) * uy + (D == 3 ? cz(i) * uz : 0.0);
     const double gh = wgt<Q>(i) * (ph1 + kq * (3.0 * cu + 4.5 * cu * cu - 1.5 * uu));
-    ((St *)a.pop_out)[i * N + n] = (St)gh;
+    ((St *)a.pop_out)[i * N + n] = store_cast<St>(gh);
   }
 }
 
