@@ -13,42 +13,52 @@
 
 namespace lbm {
 
+// Cell of this thread (256 consecutive ones per block, each XCD on a contiguous part of the
+// grid) and the offsets of its periodic neighbours at -2..2 on each axis.
+template <class A> __device__ __forceinline__ int adjoint_cell(const A &a, int (&off)[3][5]) {
+  const int nxy = a.nx * a.ny;
+  const int n = tile_of_block(blockIdx.x, gridDim.x, a.remap) * 256 + (int)threadIdx.x;
+  const int z = n / nxy, rem = n - z * nxy, y = rem / a.nx, x = rem - y * a.nx;
+  int code[5];
+  axis_offsets(x, a.nx, -1, -1, 1, off[0], code);
+  axis_offsets(y, a.ny, -1, -1, a.nx, off[1], code);
+  axis_offsets(z, a.nz, -1, -1, nxy, off[2], code);
+  return n;
+}
+// Index of the cell at -c_i.
+__device__ __forceinline__ unsigned adjoint_source(unsigned un, int i, const int (&off)[3][5]) {
+  return un + (unsigned)(off[0][2 - cx(i)] + off[1][2 - cy(i)] + off[2][2 - cz(i)]);
+}
+
+// One reverse step of a cell.  Bound by memory: the populations, their adjoint in and out, and
+// the 13 coefficients of the scalar (440 B per FP32 cell) at two waves per SIMD (three 27-vectors
+// live; asked for three waves it spills and takes 225 us).  All accesses are raw buffer ones
+// with shared 32-bit offsets, the stencil loads its three upwind neighbours instead of four, and
+// FP32 streams the incoming adjoint, which is read once (FP64, at one wave, measured slower
+// so).  FP32 us per step, passive 128^3 198 -> 190 (4.9 TB/s), isothermal 128^3 153 -> 142,
+// passive 100x90x110 101 -> 93, 40^3 13.1 -> 11.6; on the step's 64x4 tiles with scalar y and
+// z the passive one took 204.
 template <int PREC, int NS>
 __global__ __launch_bounds__(256) void adjoint_kernel(KArgs<typename Prec<PREC>::R> a,
-                                                      const typename Prec<PREC>::R *__restrict__ lamB,
-                                                      const typename Prec<PREC>::R *__restrict__ lamT1,
-                                                      typename Prec<PREC>::R *__restrict__ lamA,
-                                                      typename Prec<PREC>::R *__restrict__ coef) {
+                    const typename Prec<PREC>::R *__restrict__ lamB,
+                    const typename Prec<PREC>::R *__restrict__ lamT1, typename Prec<PREC>::R *__restrict__ lamA,
+                    typename Prec<PREC>::R *__restrict__ coef) {
   using P = Prec<PREC>;
   using St = typename P::St;
   using R = typename P::R;
   using Sc = typename P::Sc;
   constexpr R s = R(1.0 / 3.0);
-  const int n = blockIdx.x * (int)blockDim.x + (int)threadIdx.x;
   const int N = a.N;
+  int off[3][5];
+  const int n = adjoint_cell(a, off);
   if (n >= N) return;
   const unsigned un = (unsigned)n;
   const St *__restrict__ pin = (const St *)a.pop_in;
-  const Sc *__restrict__ sin_ = (const Sc *)a.scal_in;
-  const int nxy = a.nx * a.ny;
-  const int z = n / nxy, rem = n - z * nxy, y = rem / a.nx, x = rem - y * a.nx;
-  int off[3][5];
-  {
-    const AxisNb ax = axis_nb(x, a.nx, -1, -1), ay = axis_nb(y, a.ny, -1, -1), az = axis_nb(z, a.nz, -1, -1);
-#pragma unroll
-    for (int k = 0; k < 5; ++k) {
-      off[0][k] = ax.idx[k] - x;
-      off[1][k] = (ay.idx[k] - y) * a.nx;
-      off[2][k] = (az.idx[k] - z) * nxy;
-    }
-  }
+  const auto sT = slice(a.scal_in);
   // pull (forward recompute)
   R g[27];
 #pragma unroll
-  for (int i = 0; i < 27; ++i) {
-    const unsigned m = un + (unsigned)(off[0][2 - cx(i)] + off[1][2 - cy(i)] + off[2][2 - cz(i)]);
-    g[i] = decode<R>(ldg(pin + (size_t)i * N, m));
-  }
+  for (int i = 0; i < 27; ++i) g[i] = decode<R>(bld<St>(slice(pin + (size_t)i * N), adjoint_source(un, i, off)));
   const R rho0 = a.th.rho_ref;
   const R mom = fdiv(a.P0, s * rho0);
   R mx = R(0), my = R(0), mz = R(0);
@@ -62,33 +72,34 @@ __global__ __launch_bounds__(256) void adjoint_kernel(KArgs<typename Prec<PREC>:
   R lu[3] = {R(0), R(0), R(0)};
   if constexpr (NS == 1) {
     // T' = T + K lap T - sum_d |u_d| W_d: adjoint of the advection part, per axis
-    const R T0 = (R)ldg(sin_, un);
-    const R lT = lamT1[n];
+    const R T0 = (R)bld<Sc>(sT, un);
+    const R lT = bld<R>(slice(lamT1), un);
     R self = R(0);
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-      const R vp1 = (R)ldg(sin_, un + (unsigned)off[d][3]), vm1 = (R)ldg(sin_, un + (unsigned)off[d][1]);
-      const R vp2 = (R)ldg(sin_, un + (unsigned)off[d][4]), vm2 = (R)ldg(sin_, un + (unsigned)off[d][0]);
       const bool up = u[d] >= R(0);
-      const R U2 = up ? vm2 : vp2, U1 = up ? vm1 : vp1, D1 = up ? vp1 : vm1;
+      // the three upwind-ordered neighbours of the stencil
+      const R U1 = (R)bld<Sc>(sT, un + (unsigned)(up ? off[d][1] : off[d][3]));
+      const R D1 = (R)bld<Sc>(sT, un + (unsigned)(up ? off[d][3] : off[d][1]));
+      const R U2 = (R)bld<Sc>(sT, un + (unsigned)(up ? off[d][0] : off[d][4]));
       R dW[4];
       const R W = weno3_diff_grad(U2, U1, T0, D1, a.eps[0], dW);
       lu[d] += up ? -lT * W : lT * W;               // d(-|u| W)/du = -sign(u) W
       const R c = -lT * fabs(u[d]);
       // contributions to the positions -2, -1, +1, +2 along d (and to the cell itself)
       const R cU2 = c * dW[0], cU1 = c * dW[1], cD1 = c * dW[3];
-      coef[(4 * d + 0) * N + n] = up ? cU2 : R(0);
-      coef[(4 * d + 1) * N + n] = up ? cU1 : cD1;
-      coef[(4 * d + 2) * N + n] = up ? cD1 : cU1;
-      coef[(4 * d + 3) * N + n] = up ? R(0) : cU2;
+      bst<R>(slice(coef + (size_t)(4 * d + 0) * N), un, up ? cU2 : R(0));
+      bst<R>(slice(coef + (size_t)(4 * d + 1) * N), un, up ? cU1 : cD1);
+      bst<R>(slice(coef + (size_t)(4 * d + 2) * N), un, up ? cD1 : cU1);
+      bst<R>(slice(coef + (size_t)(4 * d + 3) * N), un, up ? R(0) : cU2);
       self += c * dW[2];
     }
-    coef[12 * N + n] = self;
+    bst<R>(slice(coef + (size_t)12 * N), un, self);
   }
   // collision reverse pass
   R lam[27];
 #pragma unroll
-  for (int i = 0; i < 27; ++i) lam[i] = lamB[i * N + n];
+  for (int i = 0; i < 27; ++i) lam[i] = bld<R, PREC == 0 ? 0 : 2>(slice(lamB + (size_t)i * N), un);
   Rates<R> rt;
   rt.tau0 = viscosity(a.th, rho0) * R(3) + R(0.5);
   rt.smag18 = a.smag18;
@@ -99,10 +110,7 @@ __global__ __launch_bounds__(256) void adjoint_kernel(KArgs<typename Prec<PREC>:
   collide_d3q27_vjp(g, mom, rt, lam, lu);
   // transposed streaming: the adjoint of g_i(r) = A_i(r - c_i) is pushed to r - c_i
 #pragma unroll
-  for (int i = 0; i < 27; ++i) {
-    const unsigned m = un + (unsigned)(off[0][2 - cx(i)] + off[1][2 - cy(i)] + off[2][2 - cz(i)]);
-    stg(lamA + (size_t)i * N, m, lam[i]);
-  }
+  for (int i = 0; i < 27; ++i) bst<R>(slice(lamA + (size_t)i * N), adjoint_source(un, i, off), lam[i]);
 }
 
 // lamT(s) = lamT'(s) + K lap(lamT')(s) + self(s) + gathered advection contributions.
@@ -112,33 +120,27 @@ __global__ __launch_bounds__(256) void adjoint_scalar_kernel(KArgs<typename Prec
                                                              const typename Prec<PREC>::R *__restrict__ coef,
                                                              typename Prec<PREC>::R *__restrict__ lamT) {
   using R = typename Prec<PREC>::R;
-  const int n = blockIdx.x * (int)blockDim.x + (int)threadIdx.x;
   const int N = a.N;
-  if (n >= N) return;
-  const int nxy = a.nx * a.ny;
-  const int z = n / nxy, rem = n - z * nxy, y = rem / a.nx, x = rem - y * a.nx;
-  const AxisNb ax = axis_nb(x, a.nx, -1, -1), ay = axis_nb(y, a.ny, -1, -1), az = axis_nb(z, a.nz, -1, -1);
   int off[3][5];
-#pragma unroll
-  for (int k = 0; k < 5; ++k) {
-    off[0][k] = ax.idx[k] - x;
-    off[1][k] = (ay.idx[k] - y) * a.nx;
-    off[2][k] = (az.idx[k] - z) * nxy;
-  }
+  const int n = adjoint_cell(a, off);
+  if (n >= N) return;
+  const unsigned un = (unsigned)n;
   const R rho0 = a.th.rho_ref;
   const R rhoD0 = rho0 * viscosity(a.th, rho0) * a.th.inv_Pr;
   const R K = fdiv(a.th.F, rho0) * rhoD0;
-  const R l0 = lamT1[n];
-  R lap = R(0), acc = coef[12 * N + n];
+  const auto sl = slice(lamT1);
+  const R l0 = bld<R>(sl, un);
+  R lap = R(0), acc = bld<R>(slice(coef + (size_t)12 * N), un);
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    lap += lamT1[n + off[d][3]] + lamT1[n + off[d][1]] - R(2) * l0;
-    acc += coef[(4 * d + 0) * N + n + off[d][4]];      // from the cell at +2 (its -2 slot)
-    acc += coef[(4 * d + 1) * N + n + off[d][3]];      // from +1 (its -1 slot)
-    acc += coef[(4 * d + 2) * N + n + off[d][1]];      // from -1 (its +1 slot)
-    acc += coef[(4 * d + 3) * N + n + off[d][0]];      // from -2 (its +2 slot)
+    lap += bld<R>(sl, un + (unsigned)off[d][3]) + bld<R>(sl, un + (unsigned)off[d][1]) - R(2) * l0;
+    auto from = [&](int j, int k) { return bld<R>(slice(coef + (size_t)(4 * d + j) * N), un + (unsigned)off[d][k]); };
+    acc += from(0, 4);      // from the cell at +2 (its -2 slot)
+    acc += from(1, 3);      // from +1 (its -1 slot)
+    acc += from(2, 1);      // from -1 (its +1 slot)
+    acc += from(3, 0);      // from -2 (its +2 slot)
   }
-  lamT[n] = l0 + K * lap + acc;
+  bst<R>(slice(lamT), un, l0 + K * lap + acc);
 }
 
 // Objective pieces at the state: block records of (rho|u|^2/2, T, T^2).
@@ -224,14 +226,14 @@ hipError_t launch_adjoint_p(int ns, int kind, const StepArgs &sa, int nblocks, h
   using R = typename Prec<PREC>::R;
   KArgs<R> a = to_kargs<R>(sa);
   if (kind == 0) {   // adjoint step
-    if (ns == 0)
+    if (ns == 0) {
       hipLaunchKernelGGL((adjoint_kernel<PREC, 0>), dim3(nblocks), dim3(256), 0, st, a, (const R *)p0, (const R *)p1,
                          (R *)p2, (R *)p4);
-    else {
+    } else {
       hipLaunchKernelGGL((adjoint_kernel<PREC, 1>), dim3(nblocks), dim3(256), 0, st, a, (const R *)p0, (const R *)p1,
                          (R *)p2, (R *)p4);
-      hipLaunchKernelGGL((adjoint_scalar_kernel<PREC>), dim3(nblocks), dim3(256), 0, st, a, (const R *)p1,
-                         (const R *)p4, (R *)p3);
+      hipLaunchKernelGGL((adjoint_scalar_kernel<PREC>), dim3(nblocks), dim3(256), 0, st, a, (const R *)p1, (const R *)p4,
+                         (R *)p3);
     }
   } else if (kind == 1 || kind == 2) {   // objective pass 0 (sums) / pass 1 (gradient)
     if (ns == 0)
