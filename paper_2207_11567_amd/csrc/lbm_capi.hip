@@ -909,7 +909,7 @@ lbm_status lbm_flame_surface(lbm_solver *s, double T_u, double T_b, double *surf
   a.scal_in = s->scal[s->cur];
   a.partials = s->aux;
   hipError_t e = launch_surface(s->Q, s->prec, a, s->nblocks, s->stream, T_u, T_b);
-  if (e == hipSuccess) e = launch_finalize(s->aux, s->nblocks, s->stage, s->sums, s->stream, head_of(s), s->host);
+  if (e == hipSuccess) e = launch_finalize_one(s->aux, s->nblocks, s->stage, s->sums, s->stream, head_of(s), s->host);
   if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
   if (e != hipSuccess) return hip_fail(s, e, "flame surface");
   *surface_host = s->host[HEAD_SUMS];
@@ -942,7 +942,7 @@ lbm_status lbm_flame_surface_noalloc(lbm_solver *s, double T_u, double T_b, doub
   a.partials = s->scratch;
   hipError_t e = launch_surface(s->Q, s->prec, a, s->nblocks, s->stream, T_u, T_b);
   if (e == hipSuccess)
-    e = launch_finalize(s->scratch, s->nblocks, s->scratch + NOALLOC_STAGE, s->scratch + NOALLOC_OUT, s->stream);
+    e = launch_finalize_one(s->scratch, s->nblocks, s->scratch + NOALLOC_STAGE, s->scratch + NOALLOC_OUT, s->stream);
   if (e == hipSuccess) {
     hipLaunchKernelGGL(copy_first_kernel, dim3(1), dim3(64), 0, s->stream, (const double *)(s->scratch + NOALLOC_OUT),
                        surface_dev);

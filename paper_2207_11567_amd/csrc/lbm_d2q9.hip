@@ -35,19 +35,30 @@ hipError_t launch_geometry_levelset(int Q, const double *phi, void *geom, int nx
   return geometry(Q, phi, geom, nx, ny, nz, N, f, st);
 }
 
-hipError_t launch_finalize(const double *partials, int nrec, double *stage, double *out, hipStream_t st,
-                           const double *head, double *host) {
+template <int W>
+static hipError_t reduce(const double *rec, int nrec, double *stage, double *out, hipStream_t st, const double *head,
+                         double *host) {
   // one launch up to 4096 records; more in chunks of at least 512 (at most 256 of them) first
   if (nrec > 4096) {
     const int chunk = nrec > 512 * 256 ? (nrec + 255) / 256 : 512;
     const int nb = (nrec + chunk - 1) / chunk;
-    hipLaunchKernelGGL(reduce_records, dim3(nb), dim3(1024), 0, st, partials, nrec, chunk, stage, (const double *)nullptr,
+    hipLaunchKernelGGL(reduce_records<W>, dim3(nb), dim3(1024), 0, st, rec, nrec, chunk, stage, (const double *)nullptr,
                        (double *)nullptr);
-    partials = stage;
+    rec = stage;
     nrec = nb;
   }
-  hipLaunchKernelGGL(reduce_records, dim3(1), dim3(1024), 0, st, partials, nrec, nrec, out, head, host);
+  hipLaunchKernelGGL(reduce_records<W>, dim3(1), dim3(1024), 0, st, rec, nrec, nrec, out, head, host);
   return hipGetLastError();
+}
+
+hipError_t launch_finalize(const double *partials, int nrec, double *stage, double *out, hipStream_t st,
+                           const double *head, double *host) {
+  return reduce<NSUM>(partials, nrec, stage, out, st, head, host);
+}
+
+hipError_t launch_finalize_one(const double *partials, int nrec, double *stage, double *out, hipStream_t st,
+                               const double *head, double *host) {
+  return reduce<1>(partials, nrec, stage, out, st, head, host);
 }
 
 hipError_t launch_publish(const double *head, double *host, hipStream_t st) {

@@ -34,6 +34,8 @@ hipError_t launch_adjoint(int prec, int ns, int kind, const StepArgs &sa, int nb
 // head (out is then its sums), the head to the host.
 hipError_t launch_finalize(const double *partials, int nrec, double *stage, double *out, hipStream_t st,
                            const double *head = nullptr, double *host = nullptr);
+hipError_t launch_finalize_one(const double *partials, int nrec, double *stage, double *out, hipStream_t st,
+                               const double *head = nullptr, double *host = nullptr);   // one counter per record
 hipError_t launch_publish(const double *head, double *host, hipStream_t st);
 // Two arrays (bytes multiples of 16, 16-byte aligned) copied in one launch, and the head.
 hipError_t launch_copy_state(const void *a, void *da, size_t abytes, const void *b, void *db, size_t bbytes,
@@ -41,7 +43,7 @@ hipError_t launch_copy_state(const void *a, void *da, size_t abytes, const void 
 hipError_t launch_set_thermo(double *thermo, double pi, double q, double K, hipStream_t st);
 // Closed domain: (pi, q, K) of the next level from the step's nrec block records.
 hipError_t launch_thermo(const double *partials, int nrec, double *thermo, hipStream_t st);
-// Observables: flame-surface block records (slot 0 of the partials) and mean / RMS fields.
+// Observables: flame-surface block records (one double each) and mean / RMS fields.
 hipError_t launch_surface(int Q, int prec, const StepArgs &a, int nblocks, hipStream_t st, double T_u, double T_b);
 hipError_t launch_statistics(const double *acc, int D, long long N, long long k, double P0, double *mean, double *rms,
                              hipStream_t st);

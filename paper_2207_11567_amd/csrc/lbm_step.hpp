@@ -470,21 +470,23 @@ __global__ __launch_bounds__(256) void split_kernel(KArgs<typename Prec<PREC>::R
 // each piece cost a launch and a staging wait of its own).
 constexpr int HEAD_WORDS = 32, HEAD_SUMS = 8;
 
-// Deterministic reduction of block records, nrec x NSUM doubles read as one contiguous run:
-// thread t of the first 1017 (a multiple of NSUM) adds elements t, t + 1017, ..., all of one
-// counter, then wave k combines counter k.  Each block sums `chunk` records; the order of
+// Deterministic reduction of block records, nrec x W doubles (W = NSUM counters, or one) read
+// as one contiguous run: thread t of the first 1017 (the largest multiple of NSUM; all 1024
+// for one counter) adds elements t, t + 1017, ..., all of one counter, then wave k combines
+// counter k.  Each block sums `chunk` records; the order of
 // every addition is fixed by the launch shape, so results are bitwise repeatable.  With a
 // host copy (one block, out in the work buffer's head) the whole head goes there too.
 // Records read as rows of NSUM by 256 threads and summed in two launches took 9 us for the
 // 1024..4900 records of the 2-D workloads, this one 4 to 6.
+template <int W>
 static __global__ __launch_bounds__(1024) void reduce_records(const double *in, int nrec, int chunk, double *out,
                                                               const double *head, double *host) {
-  constexpr int USED = 1024 / NSUM * NSUM, GROUPS = USED / NSUM;
+  constexpr int USED = 1024 / W * W, GROUPS = USED / W;
   __shared__ double sh[USED];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const long long b0 = (long long)blockIdx.x * chunk;
-  const int count = (int)min((long long)chunk, nrec - b0) * NSUM;
-  const double *rec = in + b0 * NSUM;
+  const int count = (int)min((long long)chunk, nrec - b0) * W;
+  const double *rec = in + b0 * W;
   if (t < USED) {
     double acc = 0.0;
 #pragma unroll 8
@@ -492,16 +494,16 @@ static __global__ __launch_bounds__(1024) void reduce_records(const double *in, 
     sh[t] = acc;
   }
   __syncthreads();
-  if (w < NSUM) {
+  if (w < W) {
     double acc = 0.0;
-    for (int j = lane; j < GROUPS; j += 64) acc += sh[j * NSUM + w];
+    for (int j = lane; j < GROUPS; j += 64) acc += sh[j * W + w];
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
     if (lane == 0) {
-      out[(size_t)blockIdx.x * NSUM + w] = acc;
+      out[(size_t)blockIdx.x * W + w] = acc;
       if (host) host[HEAD_SUMS + w] = acc;
     }
   }
-  if (host && t < HEAD_WORDS && (t < HEAD_SUMS || t >= HEAD_SUMS + NSUM)) host[t] = head[t];
+  if (host && t < HEAD_WORDS && (t < HEAD_SUMS || t >= HEAD_SUMS + W)) host[t] = head[t];
 }
 
 // The head alone, for calls without a kernel that could pass it on.
@@ -585,45 +587,46 @@ static __global__ void set_thermo_kernel(double *thermo, double pi, double q, do
 
 // Generalised flame surface: |grad c| summed over fluid cells, c = (T - T_u)/(T_b - T_u),
 // central differences with the ghost rules of grad rho (own value across walls, solids
-// and the outlet, the inlet temperature across the inlet); FP64 block records.
+// and the outlet, the inlet temperature across the inlet); one FP64 record per block.  The
+// neighbours are loads from selected addresses, and the block sums one value by shuffles
+// instead of NSUM of them through LDS.
 template <int Q, int PREC>
 __global__ __launch_bounds__(256) void surface_kernel(KArgs<double> a, double inv_dT) {
   using Sc = typename Prec<PREC>::Sc;
   using GW = typename GeomWord<Q>::T;
   constexpr int D = Lat<Q>::D;
-  const int n = blockIdx.x * (int)blockDim.x + (int)threadIdx.x;
-  double red[NSUM];
-#pragma unroll
-  for (int k = 0; k < NSUM; ++k) red[k] = 0.0;
+  __shared__ double part[4];
+  const int n = tile_of_block(blockIdx.x, gridDim.x, a.remap) * 256 + (int)threadIdx.x;
+  double acc = 0.0;
   if (n < a.N) {
     const GW gw = a.geom ? ((const GW *)a.geom)[n] : GW(0);
-    if (!(gw & (GW(1) << bit_self<Q>()))) {
-      const Sc *T = (const Sc *)a.scal_in;
-      const int nxy = a.nx * a.ny, z = n / nxy, rem = n - z * nxy, y = rem / a.nx, x = rem - y * a.nx;
-      const int cc[3] = {x, y, z}, ext[3] = {a.nx, a.ny, a.nz};
-      const double t0 = (double)T[n];
-      double g2 = 0.0;
+    const auto sT = slice(a.scal_in);
+    const unsigned un = (unsigned)n;
+    const int nxy = a.nx * a.ny, z = n / nxy, rem = n - z * nxy, y = rem / a.nx, x = rem - y * a.nx;
+    double g2 = 0.0;
 #pragma unroll
-      for (int d = 0; d < D; ++d) {
-        const AxisNb ax = axis_nb(cc[d], ext[d], a.face[2 * d], a.face[2 * d + 1]);
-        const int stride = d == 0 ? 1 : d == 1 ? a.nx : nxy;
-        double v[2];
+    for (int d = 0; d < D; ++d) {
+      int off[5], code[5];
+      axis_offsets(d == 0 ? x : d == 1 ? y : z, d == 0 ? a.nx : d == 1 ? a.ny : a.nz, a.face[2 * d], a.face[2 * d + 1],
+                   d == 0 ? 1 : d == 1 ? a.nx : nxy, off, code);
+      double v[2];
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-          const int k = s == 0 ? 3 : 1;                    // +1, -1
-          const int code = ax.code[k];
-          const int bit = s == 0 ? link_from_plus<Q>(d) : link_from_minus<Q>(d);
-          if (code == ST_INLET) v[s] = a.phi_in[0];
-          else if (code >= 0 || ((gw >> bit) & 1)) v[s] = t0;
-          else v[s] = (double)T[n + (ax.idx[k] - cc[d]) * stride];
-        }
-        const double gd = 0.5 * (v[0] - v[1]) * inv_dT;
-        g2 += gd * gd;
+      for (int s = 0; s < 2; ++s) {
+        const int k = s == 0 ? 3 : 1;                      // +1, -1
+        const int bit = s == 0 ? link_from_plus<Q>(d) : link_from_minus<Q>(d);
+        const bool own = code[k] >= 0 || ((gw >> bit) & 1);
+        v[s] = (double)bld<Sc>(sT, own ? un : un + (unsigned)off[k]);
+        if (code[k] == ST_INLET) v[s] = a.phi_in[0];
       }
-      red[0] = sqrt(g2);
+      const double gd = 0.5 * (v[0] - v[1]) * inv_dT;
+      g2 += gd * gd;
     }
+    acc = gw & (GW(1) << bit_self<Q>()) ? 0.0 : sqrt(g2);
   }
-  block_sums(red, a.partials + (size_t)blockIdx.x * NSUM);
+  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) a.partials[blockIdx.x] = (part[0] + part[1]) + (part[2] + part[3]);
 }
 
 // Mean and RMS fields from the running statistics (k samples): mean [D+1][N] (u_d, then
