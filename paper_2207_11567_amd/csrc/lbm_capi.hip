@@ -481,8 +481,17 @@ static hipError_t launch_step_pass(lbm_solver *s, const StepArgs &a0) {
     if (e != hipSuccess) return e;
     s->side_ready = true;
   }
-  // fork: the list half waits for everything before this step on the caller's stream,
-  // then runs beside the interior half (the two write disjoint cells and records)
+  // fork and join: one half on the caller's stream, the other on the side stream, which waits
+  // for everything before this step; the two write disjoint cells and records.  The half on
+  // the caller's stream has its blocks placed first.  That is the list half where its chain
+  // is long against the interior half's time (mixture transport, and curved walls up to 8192
+  // tiles): a wave of it needs more registers than one interior wave leaves, and behind a
+  // full chip of interior blocks it waited for the end of them.  Elsewhere the interior half
+  // would only start later.  us per step, interior / list half first: burner (both)
+  // 128x128x256 419 / 389, 64x64x128 119 / 89, mixture 128^3 203 / 192; cone 64x64x128 FP64 134 /
+  // 102, 128x128x256 295 / 312; reacting box 160x160x320 507 / 517, 121x121x242 303 / 307.
+  const bool list_first = a.mix || (a.lvl && s->nblocks <= 8192);
+  const hipStream_t list_stream = list_first ? s->stream : s->side, tile_stream = list_first ? s->side : s->stream;
   StepArgs b = a;
   b.cells = s->cells;
   b.ncells = s->ncells;
@@ -491,11 +500,17 @@ static hipError_t launch_step_pass(lbm_solver *s, const StepArgs &a0) {
   e = hipEventRecord(s->ev_fork, s->stream);
   if (e == hipSuccess) e = hipStreamWaitEvent(s->side, s->ev_fork, 0);
   if (e != hipSuccess) return e;
-  e = launch_d3q27(s->prec, s->NS, LAUNCH_STEP_LIST, b, nlb, s->side, nullptr, nullptr, nullptr);
-  if (e == hipSuccess) e = hipEventRecord(s->ev_join, s->side);
-  if (e == hipSuccess) e = launch(s, LAUNCH_STEP_INTERIOR, a);
-  // join: later work on the caller's stream sees both halves
-  if (e == hipSuccess) e = hipStreamWaitEvent(s->stream, s->ev_join, 0);
+  e = launch_d3q27(s->prec, s->NS, LAUNCH_STEP_LIST, b, nlb, list_stream, nullptr, nullptr, nullptr);
+  if (e == hipSuccess)
+    e = launch_d3q27(s->prec, s->NS, LAUNCH_STEP_INTERIOR, a, s->nblocks, tile_stream, nullptr, nullptr, nullptr);
+  // join, also where a launch failed: later work on the caller's stream sees both halves
+  const hipError_t j = hipEventRecord(s->ev_join, s->side);
+  if (j == hipSuccess) {
+    const hipError_t w = hipStreamWaitEvent(s->stream, s->ev_join, 0);
+    if (e == hipSuccess) e = w;
+  } else if (e == hipSuccess) {
+    e = j;
+  }
   s->nrec = s->nblocks + nlb;
   return e;
 }
