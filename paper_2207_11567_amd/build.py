@@ -2,7 +2,10 @@
 
 Usage: python -m paper_2207_11567_amd.build   (or build() from Python).
 Compiles every translation unit under csrc/ in parallel into _build/ and links the
-shared library next to this file.  Always recompiles.
+shared library next to this file.  The step's instances, most of the work, are one object
+per lattice, precision and number of scalars (generated units that instantiate
+launch_one), which the dispatching units only refer to: about 2 minutes on 8 cores instead
+of 5 with an object per precision.  Always recompiles.
 """
 import concurrent.futures as cf
 import os
@@ -25,19 +28,42 @@ UNITS = ["lbm_capi.hip", "lbm_d2q9.hip", "lbm_d3q27.hip", "lbm_d3q27_p0.hip",
          "lbm_d3q27_p1.hip", "lbm_d3q27_p2.hip", "lbm_adjoint.hip"]
 
 
-def _compile(unit):
-    src = os.path.join(CSRC, unit)
-    obj = os.path.join(BUILD, unit.replace(".hip", ".o"))
+_ARGS = "(int, const StepArgs &, int, hipStream_t, const double *, const double *, const double *)"
+
+
+def _instances():
+    """{unit: [extra flags]} of the generated instance units, written to _build/, and the header
+    that declares them to the dispatching units; the longest compilations first."""
+    combos = [(q, p, n) for n in (6, 2, 1, 0) for q in (27, 9) for p in (0, 2, 1)]
+    head = f'#include "{CSRC}/lbm_launch.hpp"\n'
+
+    def body(word):
+        return "".join(f"{word} hipError_t launch_one<{q}, {p}, {n}>{_ARGS};\n" for q, p, n in combos)
+
+    with open(os.path.join(BUILD, "instances.hpp"), "w") as f:
+        f.write("#pragma once\n" + head + "namespace lbm {\n" + body("extern template") + "}\n")
+    units = []
+    for q, p, n in combos:
+        units.append(os.path.join(BUILD, f"step_{q}_{p}_{n}.hip"))
+        with open(units[-1], "w") as f:
+            f.write(head + f"namespace lbm {{ template hipError_t launch_one<{q}, {p}, {n}>{_ARGS}; }}\n")
+    return units
+
+
+def _compile(src):
+    obj = os.path.join(BUILD, os.path.basename(src).replace(".hip", ".o"))
     cmd = [HIPCC] + FLAGS + ["-c", src, "-o", obj]
+    if "lbm_d2q9" in src or "lbm_d3q27" in src:
+        cmd += ["-include", os.path.join(BUILD, "instances.hpp")]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
-        raise RuntimeError(f"hipcc failed for {unit}:\n{r.stderr}")
+        raise RuntimeError(f"hipcc failed for {src}:\n{r.stderr}")
     return obj
 
 
 def build(verbose=True):
     os.makedirs(BUILD, exist_ok=True)
-    units = [u for u in UNITS if os.path.exists(os.path.join(CSRC, u))]
+    units = _instances() + [os.path.join(CSRC, u) for u in UNITS]
     workers = min(len(units), max(1, min(8, os.cpu_count() or 1)))
     with cf.ThreadPoolExecutor(workers) as ex:
         objs = list(ex.map(_compile, units))
