@@ -42,7 +42,7 @@
  * pointer; the library keeps the pointers for the solver's lifetime, never frees them and
  * allocates no device memory of its own (256 bytes of pinned host memory per solver take the
  * results of the synchronising calls).  All work is ordered on the caller's HIP stream:
- * where a D3Q27 step runs split (boundary cells in a second kernel), that kernel runs on a
+ * where a D3Q27 step runs split (boundary cells in a second kernel), one of the two runs on a
  * side stream the solver creates on first use, forked from the caller's stream by an event
  * before the step and joined back into it after, so later work on the caller's stream sees
  * the whole step.  lbm_step does not synchronise, lbm_fields and the state copies do;

@@ -34,7 +34,7 @@ struct lbm_solver {
   int *cells;         // linear indices of the boundary cells (the step's list half)
   int ncells;         // their number
   int nrec;           // block records the last step wrote
-  // the list half of a split step runs on a side stream (default priority), forked from
+  // one half of a split D3Q27 step runs on a side stream (default priority), forked from
   // and joined back into the caller's stream around each step; created on first use
   hipStream_t side;
   hipEvent_t ev_fork, ev_join;

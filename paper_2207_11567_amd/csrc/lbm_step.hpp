@@ -404,7 +404,7 @@ __device__ __forceinline__ int step_cells(const KArgs<typename Prec<PREC>::R> &a
 }
 
 // One kind of cell per launch: every cell, or one half of a split step of D3Q27 (interior
-// tiles, or the listed boundary cells, which run beside them on a side stream).
+// tiles, or the listed boundary cells, two kernels side by side on two streams).
 // The FP32-arithmetic two-step D3Q27 step (FP32 or FP16 storage) asks for four waves per
 // SIMD (at most 128 VGPRs): its allocation otherwise lands a few registers above that, at
 // three waves; the few spilled values cost less than the lost wave (measured 9 % faster on
