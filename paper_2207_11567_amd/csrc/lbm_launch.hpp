@@ -72,13 +72,17 @@ hipError_t launch_step(const StepArgs &a, int nblocks, hipStream_t st) {
     case COLL_CUM1: {
       constexpr bool free = MODE == MODE_FREE || MODE == MODE_FREE_LIN;
       constexpr bool inter = MODE == MODE_INTERIOR || MODE == MODE_INTERIOR_LIN;
-      // FP32 steps without boundaries: dynamic LDS leaves five blocks a CU instead of eight.
+      // FP32 and FP64 steps without boundaries: dynamic LDS leaves five blocks a CU instead of
+      // eight (FP32) or six (FP64).
       // More waves in flight than the memory side needs cost it locality (HIT FP32, us per step
       // at 8 / 7 / 6 / 5 / 4 blocks: 256^3 667 / 660 / 646 / 643 / 643, 128^3 87.9 / 87.1 / 85.2 /
       // 84.9 / 85.2; passive 128^3 92.0 / 91.9 / 90.2 / 90.8 / 90.6).  FP16 storage, bound by
-      // issue, wants them all (377 / 380 / 396 / 422 / 425), FP64 holds six by its registers.
-      // Grids of a few passes gain nothing and a single pass loses (passive 64^3 12.8 / 14.1).
-      const unsigned lds = Q == 27 && PREC == 1 && free && nblocks >= 4096 ? 14000 : 0;
+      // issue, wants them all (377 / 380 / 396 / 422 / 425).  FP64 at 6 / 5 / 3: 256^3 1404 / 1338 /
+      // 1323, 224^3 936 / 930 / 935, 128^3 166.7 / 167.4 / 165.1 (all-cell instance, five by its
+      // registers: 1358, 922, 169.8).
+      // Grids of a few passes gain nothing and a single pass loses (passive 64^3 FP32 12.8 / 14.1, HIT 64^3 FP64 25.5 /
+      // 28.7).
+      const unsigned lds = Q == 27 && PREC != 2 && free && nblocks >= 4096 ? 14000 : 0;
       // SEG by kind of step, not by size, so that a grid rounds as its copies side by side do
       constexpr bool seg = Q == 27 && ((PREC != 0 && NS == 6 && inter) || (PREC == 2 && free)) && !FULL;
       // the plain production instances also come with cached pull loads (large grids)
