@@ -40,13 +40,14 @@
  *
  * Ownership: every device buffer is allocated by the caller and passed as a device
  * pointer; the library keeps the pointers for the solver's lifetime, never frees them and
- * allocates no device memory of its own (256 bytes of pinned host memory per solver take the
- * results of the synchronising calls).  All work is ordered on the caller's HIP stream:
- * where a D3Q27 step runs split (boundary cells in a second kernel), one of the two runs on a
- * side stream the solver creates on first use, forked from the caller's stream by an event
- * before the step and joined back into it after, so later work on the caller's stream sees
- * the whole step.  lbm_step does not synchronise, lbm_fields and the state copies do;
- * lbm_destroy waits for the side stream.
+ * allocates no device memory of its own (16 KiB of pinned host memory, held from the first
+ * solver on until the process ends, take the results of the synchronising calls of up to 64
+ * solvers at a time; further ones read them by copies).  All work is ordered on the caller's
+ * HIP stream: where a D3Q27 step runs split (boundary cells in a second kernel), one of the
+ * two runs on a side stream the solver creates on first use, forked from the caller's stream
+ * by an event before the step and joined back into it after, so later work on the caller's
+ * stream sees the whole step.  lbm_step does not synchronise, lbm_fields and the state copies do;
+ * lbm_destroy waits for the side stream, where there is one, and for nothing else.
  * Errors: every call returns an lbm_status; lbm_last_error gives a message.  A
  * non-finite value produced by a step raises a device flag reported as LBM_E_DIVERGED by
  * the next synchronising call.

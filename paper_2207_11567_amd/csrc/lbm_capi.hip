@@ -14,6 +14,41 @@
 
 using namespace lbm;
 
+// Pinned host copies of the solvers' heads, one block of HEAD_WORDS doubles for each of up to
+// HEAD_BLOCKS solvers alive at a time: one allocation of 16 KiB, made for the first solver and
+// kept until the process ends, because freeing host memory waits for every stream of the
+// device (a solver that freed its own block held up work that had nothing to do with it).  A
+// solver without a block (more of them alive, or no pinned memory) reads its head with a copy.
+constexpr int HEAD_BLOCKS = 64;
+static std::mutex g_head_mu;
+static double *g_heads = nullptr;
+static unsigned long long g_heads_taken = 0;    // bit j: block j belongs to a solver
+
+static double *take_head_block() {
+  std::lock_guard<std::mutex> lock(g_head_mu);
+  if (!g_heads) {
+    // allowed also while another stream of the process is being captured
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool changed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    void *ptr = nullptr;
+    if (hipHostMalloc(&ptr, HEAD_BLOCKS * HEAD_WORDS * sizeof(double), hipHostMallocPortable) == hipSuccess)
+      g_heads = (double *)ptr;
+    else
+      (void)hipGetLastError();
+    if (changed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+  if (!g_heads || g_heads_taken == ~0ull) return nullptr;
+  int j = 0;
+  while ((g_heads_taken >> j) & 1) ++j;
+  g_heads_taken |= 1ull << j;
+  return g_heads + (size_t)j * HEAD_WORDS;
+}
+
+static void give_head_block_back(const double *block) {
+  std::lock_guard<std::mutex> lock(g_head_mu);
+  g_heads_taken &= ~(1ull << ((block - g_heads) / HEAD_WORDS));
+}
+
 struct lbm_solver {
   lbm_params p;
   hipStream_t stream;
@@ -28,7 +63,9 @@ struct lbm_solver {
   int Q, NS, D, prec, nblocks;
   int *flag;
   double *sums;
-  double *host;       // pinned host copy of the work buffer's head (flag, sums, thermo)
+  double *host;       // pinned host copy of the work buffer's head (flag, sums, thermo) or nullptr
+  bool publishing;    // a kernel that writes it was launched and has not been waited for
+  double head[HEAD_WORDS];   // the head as the last synchronising call read it
   double *partials;   // block records of lbm_step: [nblocks] tiles, then [list blocks]
   double *aux;        // block records of field extraction, flame surface and objective
   int *cells;         // linear indices of the boundary cells (the step's list half)
@@ -40,13 +77,14 @@ struct lbm_solver {
   hipEvent_t ev_fork, ev_join;
   bool side_ready;
   ~lbm_solver() {
-    if (host) (void)hipHostFree(host);
     if (side_ready) {
       (void)hipStreamSynchronize(side);
       (void)hipEventDestroy(ev_fork);
       (void)hipEventDestroy(ev_join);
       (void)hipStreamDestroy(side);
     }
+    // after a wait that failed a kernel may still write the block: it is not used again
+    if (host && !publishing) give_head_block_back(host);
   }
   double *stage;
   double *thermo;     // (pi, q, K) of the closed-domain thermodynamic pressure
@@ -356,13 +394,31 @@ static hipError_t launch(const lbm_solver *s, int kind, const StepArgs &a, const
   return launch_d3q27(s->prec, s->NS, kind, a, s->nblocks, s->stream, Ph, u, scal);
 }
 
-// Waits for the stream, whose last kernel has put the head into the host copy, and looks at
-// the divergence flag there.
+static const double *head_of(const lbm_solver *s) { return (const double *)s->work; }
+
+// Where the last kernel of a synchronising call puts the head (nullptr: nowhere, read_head
+// copies it).
+static double *publish_to(lbm_solver *s) {
+  s->publishing = s->host != nullptr;
+  return s->host;
+}
+
+// Waits for the stream and takes over the head that the call's last kernel has published.
+static hipError_t read_head(lbm_solver *s) {
+  hipError_t e = hipSuccess;
+  if (!s->host) e = hipMemcpyAsync(s->head, s->work, sizeof s->head, hipMemcpyDeviceToHost, s->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
+  if (e != hipSuccess) return e;
+  if (s->host) memcpy(s->head, s->host, sizeof s->head);
+  s->publishing = false;
+  return hipSuccess;
+}
+
 static lbm_status wait_and_check(lbm_solver *s) {
-  const hipError_t e = hipStreamSynchronize(s->stream);
+  const hipError_t e = read_head(s);
   if (e != hipSuccess) return hip_fail(s, e, "waiting for the stream");
   int f = 0;
-  memcpy(&f, s->host, sizeof f);
+  memcpy(&f, s->head, sizeof f);
   if (f & 1) {
     s->err = "a non-finite value appeared during a time step";
     return LBM_E_DIVERGED;
@@ -370,11 +426,9 @@ static lbm_status wait_and_check(lbm_solver *s) {
   return LBM_OK;
 }
 
-static const double *head_of(const lbm_solver *s) { return (const double *)s->work; }
-
 static lbm_status wait_for_sums(lbm_solver *s, double *sums_host) {
   const lbm_status st = wait_and_check(s);
-  if (sums_host && st != LBM_E_HIP) memcpy(sums_host, s->host + HEAD_SUMS, 8 * sizeof(double));
+  if (sums_host && st != LBM_E_HIP) memcpy(sums_host, s->head + HEAD_SUMS, 8 * sizeof(double));
   return st;
 }
 
@@ -391,7 +445,7 @@ static bool local_memory(const void *p, size_t bytes) {
 }
 
 static lbm_status check_flag(lbm_solver *s) {
-  const hipError_t e = launch_publish(head_of(s), s->host, s->stream);
+  const hipError_t e = launch_publish(head_of(s), publish_to(s), s->stream);
   if (e != hipSuccess) return hip_fail(s, e, "reading the divergence flag");
   return wait_and_check(s);
 }
@@ -649,10 +703,10 @@ lbm_status lbm_create(const lbm_params *p, void *stream, void *pop_a, void *pop_
   s->nprobe = 0;
   s->probe_cap = s->probe_rows = 0;
   s->geom = s->work + L.off_geom;
-  s->host = nullptr;
+  s->host = take_head_block();
+  s->publishing = false;
   s->scratch = scratch_on_current_device(s->scratch_err);   // the solver's device is the current one
-  hipError_t e = hipHostMalloc((void **)&s->host, HEAD_WORDS * sizeof(double), hipHostMallocDefault);
-  if (e == hipSuccess) e = hipMemsetAsync(s->work, 0, 256, s->stream);
+  hipError_t e = hipMemsetAsync(s->work, 0, 256, s->stream);
   if (e == hipSuccess) e = launch_set_thermo(s->thermo, 1.0, 0.0, 0.0, s->stream);
   if (e == hipSuccess) e = build_cell_list(s);
   if (e != hipSuccess) {
@@ -785,7 +839,7 @@ lbm_status lbm_step_from(lbm_solver *s, const void *pops_in, const void *scal_in
 
 lbm_status lbm_step_sums(lbm_solver *s, double *sums_host) {
   if (!s) return LBM_E_INVALID;
-  hipError_t e = launch_finalize(s->partials, s->nrec, s->stage, s->sums, s->stream, head_of(s), s->host);
+  hipError_t e = launch_finalize(s->partials, s->nrec, s->stage, s->sums, s->stream, head_of(s), publish_to(s));
   if (e != hipSuccess) return hip_fail(s, e, "finalize kernel");
   return wait_for_sums(s, sums_host);
 }
@@ -806,7 +860,7 @@ lbm_status lbm_fields(lbm_solver *s, double *P_h, double *rho, double *u, double
   a.partials = s->aux;                  // the step's own records stay for lbm_step_sums
   hipError_t e = launch(s, LAUNCH_EXTRACT, a);
   if (e != hipSuccess) return hip_fail(s, e, "field extraction kernel");
-  e = launch_finalize(s->aux, s->nblocks, s->stage, s->sums, s->stream, head_of(s), s->host);
+  e = launch_finalize(s->aux, s->nblocks, s->stage, s->sums, s->stream, head_of(s), publish_to(s));
   if (e != hipSuccess) return hip_fail(s, e, "finalize kernel");
   return wait_for_sums(s, sums_host);
 }
@@ -818,8 +872,8 @@ lbm_status lbm_get_state(lbm_solver *s, void *pops_dst, void *scal_dst, int64_t 
   const bool scal = scal_dst && sb;
   if (pops_dst && local_memory(pops_dst, pb) && local_memory(s->pop[s->cur], pb) &&
       (!scal || (local_memory(scal_dst, sb) && local_memory(s->scal[s->cur], sb)))) {
-    e = launch_copy_state(s->pop[s->cur], pops_dst, pb, s->scal[s->cur], scal_dst, scal ? sb : 0, head_of(s), s->host,
-                          s->stream);
+    e = launch_copy_state(s->pop[s->cur], pops_dst, pb, s->scal[s->cur], scal_dst, scal ? sb : 0, head_of(s),
+                          publish_to(s), s->stream);
     if (e != hipSuccess) return hip_fail(s, e, "copying the state out");
     if (step) *step = s->step;
     return wait_and_check(s);
@@ -924,10 +978,10 @@ lbm_status lbm_flame_surface(lbm_solver *s, double T_u, double T_b, double *surf
   a.scal_in = s->scal[s->cur];
   a.partials = s->aux;
   hipError_t e = launch_surface(s->Q, s->prec, a, s->nblocks, s->stream, T_u, T_b);
-  if (e == hipSuccess) e = launch_finalize_one(s->aux, s->nblocks, s->stage, s->sums, s->stream, head_of(s), s->host);
-  if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
+  if (e == hipSuccess) e = launch_finalize_one(s->aux, s->nblocks, s->stage, s->sums, s->stream, head_of(s), publish_to(s));
+  if (e == hipSuccess) e = read_head(s);
   if (e != hipSuccess) return hip_fail(s, e, "flame surface");
-  *surface_host = s->host[HEAD_SUMS];
+  *surface_host = s->head[HEAD_SUMS];
   return LBM_OK;
 }
 
@@ -999,10 +1053,10 @@ lbm_status lbm_copy_probe(const void *src, void *dst, size_t bytes, int32_t mode
 
 lbm_status lbm_get_thermo_pressure(lbm_solver *s, double *pqk_host) {
   if (!s || !pqk_host) return LBM_E_INVALID;
-  hipError_t e = launch_publish(head_of(s), s->host, s->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
+  hipError_t e = launch_publish(head_of(s), publish_to(s), s->stream);
+  if (e == hipSuccess) e = read_head(s);
   if (e != hipSuccess) return hip_fail(s, e, "reading the thermodynamic pressure");
-  memcpy(pqk_host, s->host + (s->thermo - s->sums) + HEAD_SUMS, 3 * sizeof(double));
+  memcpy(pqk_host, s->head + (s->thermo - s->sums) + HEAD_SUMS, 3 * sizeof(double));
   return LBM_OK;
 }
 
@@ -1096,10 +1150,10 @@ lbm_status lbm_objective(lbm_solver *s, const void *state_pops, const void *stat
                                 nullptr, 0.0, nullptr, nullptr);
   if (e != hipSuccess) return hip_fail(s, e, "objective sums");
   double sums[8];
-  e = launch_finalize(s->aux, s->nblocks, s->stage, s->sums, s->stream, head_of(s), s->host);
-  if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
+  e = launch_finalize(s->aux, s->nblocks, s->stage, s->sums, s->stream, head_of(s), publish_to(s));
+  if (e == hipSuccess) e = read_head(s);
   if (e != hipSuccess) return hip_fail(s, e, "objective sums");
-  memcpy(sums, s->host + HEAD_SUMS, sizeof sums);
+  memcpy(sums, s->head + HEAD_SUMS, sizeof sums);
   const double mean_T = sums[1] / (double)s->N;
   if (J_host) *J_host = sums[0] + (s->NS ? sums[2] - sums[1] * mean_T : 0.0);
   if (adj_pop_out) {

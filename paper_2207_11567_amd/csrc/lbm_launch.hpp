@@ -36,7 +36,7 @@ hipError_t launch_finalize(const double *partials, int nrec, double *stage, doub
                            const double *head = nullptr, double *host = nullptr);
 hipError_t launch_finalize_one(const double *partials, int nrec, double *stage, double *out, hipStream_t st,
                                const double *head = nullptr, double *host = nullptr);   // one counter per record
-hipError_t launch_publish(const double *head, double *host, hipStream_t st);
+hipError_t launch_publish(const double *head, double *host, hipStream_t st);   // nothing without a host copy
 // Two arrays (bytes multiples of 16, 16-byte aligned) copied in one launch, and the head.
 hipError_t launch_copy_state(const void *a, void *da, size_t abytes, const void *b, void *db, size_t bbytes,
                              const double *head, double *host, hipStream_t st);

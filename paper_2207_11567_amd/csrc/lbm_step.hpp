@@ -466,8 +466,8 @@ __global__ __launch_bounds__(256) void split_kernel(KArgs<typename Prec<PREC>::R
 
 // The first bytes of the work buffer (divergence flag at 0, final sums at 64, thermodynamic
 // pressure at 192): 32 doubles that the synchronising calls hand to the host, written by a
-// kernel of the call straight into the solver's pinned host copy (a device-to-host copy of
-// each piece cost a launch and a staging wait of its own).
+// kernel of the call straight into the solver's pinned host copy, where it has one (a
+// device-to-host copy of each piece cost a launch and a staging wait of its own).
 constexpr int HEAD_WORDS = 32, HEAD_SUMS = 8;
 
 // Deterministic reduction of block records, nrec x W doubles (W = NSUM counters, or one) read
@@ -532,7 +532,7 @@ template <bool STREAM>
 __global__ __launch_bounds__(256) void copy_state_kernel(const u32x4 *a, u32x4 *da, size_t na, const u32x4 *b, u32x4 *db,
                                                          size_t nb, const double *head, double *host) {
   const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x, stride = (size_t)gridDim.x * 256;
-  if (i < HEAD_WORDS) host[i] = head[i];
+  if (host && i < HEAD_WORDS) host[i] = head[i];
   copy_words<STREAM>(a, da, na, i, stride);
   copy_words<STREAM>(b, db, nb, i, stride);
 }
