@@ -265,7 +265,7 @@ lbm_status lbm_flame_surface(lbm_solver *s, double T_u, double T_b, double *surf
 /* The flame surface of lbm_flame_surface, for callers that cannot allocate or synchronise
  * (code under HIP graph capture, tight serving loops, harnesses that forbid allocation):
  * allocates nothing and does not synchronise.  Its partial sums live in a device scratch
- * array of the library (about 9.5 MB per device, held until the process ends), not in the
+ * array of the library (1 MiB per device, held until the process ends), not in the
  * solver's work buffer; grids up to 131072 blocks of 256 cells (33,554,432 cells) are
  * accepted, larger ones return LBM_E_INVALID.  The sum (FP64, bit for bit the value
  * lbm_flame_surface returns) is written to surface_dev, a device double, in stream order.

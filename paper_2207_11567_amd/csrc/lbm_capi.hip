@@ -571,15 +571,15 @@ static hipError_t launch_step_pass(lbm_solver *s, const StepArgs &a0) {
 
 // ------------------------------------------------------------------ allocation-free surface
 // Device scratch of lbm_flame_surface_noalloc, held by the library on every device it runs
-// on until the process ends: the surface kernel's block records [NOALLOC_MAX_BLOCKS][NSUM],
-// then the 256 stage records of the two-stage sum, then the NSUM final sums.  Every record
-// a call reads was written earlier in the same call, so nothing needs clearing.  In host
+// on until the process ends: the surface kernel's block records, one double each, then the
+// 256 stage records of the two-stage sum, then the sum (1 MiB).  Every record a call
+// reads was written earlier in the same call, so nothing needs clearing.  In host
 // code the name `scratch` only stands in for the symbol: its device address comes from
 // hipGetSymbolAddress, once per device, and is kept in g_scratch_ptr.
 constexpr int NOALLOC_MAX_BLOCKS = 131072;                        // 33.5 M cells, 256 per block
-constexpr size_t NOALLOC_STAGE = (size_t)NOALLOC_MAX_BLOCKS * NSUM;
-constexpr size_t NOALLOC_OUT = NOALLOC_STAGE + (size_t)256 * NSUM;
-static __device__ __align__(256) double scratch[NOALLOC_OUT + NSUM];
+constexpr size_t NOALLOC_STAGE = NOALLOC_MAX_BLOCKS;
+constexpr size_t NOALLOC_OUT = NOALLOC_STAGE + 256;
+static __device__ __align__(256) double scratch[NOALLOC_OUT + 1];
 
 constexpr int NOALLOC_MAX_DEVICES = 64;
 static std::mutex g_scratch_mu;
