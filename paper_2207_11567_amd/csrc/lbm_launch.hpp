@@ -85,25 +85,27 @@ hipError_t launch_step(const StepArgs &a, int nblocks, hipStream_t st) {
       const unsigned lds = Q == 27 && PREC != 2 && free && nblocks >= 4096 ? 14000 : 0;
       // SEG by kind of step, not by size, so that a grid rounds as its copies side by side do
       constexpr bool seg = Q == 27 && ((PREC != 0 && NS == 6 && inter) || (PREC == 2 && free)) && !FULL;
-      // the plain production instances also come with cached pull loads (large grids)
-      if constexpr (!FULL && MODE != MODE_LIST) {
-        if (seg && !a.lvl) {
-          if (a.pull_cached)
-            hipLaunchKernelGGL((step_kernel<Q, PREC, NS, false, false, COLL_CUM1, MODE, true, seg>), dim3(nblocks),
-                               dim3(256), 0, st, to_kargs<R>(a));
-          else
-            hipLaunchKernelGGL((step_kernel<Q, PREC, NS, false, false, COLL_CUM1, MODE, false, seg>), dim3(nblocks),
-                               dim3(256), 0, st, to_kargs<R>(a));
-          break;
+      // The plain instances also come with cached pull loads (large grids): the interior ones, and
+      // with fewer than two scalars those of every cell (more scalars split on such grids).
+      constexpr bool cached = !FULL && MODE != MODE_LIST && (inter || NS < 2);
+      auto run = [&](auto pullc, auto segment) {
+        hipLaunchKernelGGL((step_kernel<Q, PREC, NS, false, FULL, COLL_CUM1, MODE, decltype(pullc)::value,
+                                        decltype(segment)::value>), dim3(nblocks), dim3(256), lds, st, to_kargs<R>(a));
+      };
+      auto run_pull = [&](auto segment) {
+        if constexpr (cached) {
+          if (a.pull_cached) return run(std::true_type{}, segment);
         }
-        if (a.pull_cached) {
-          hipLaunchKernelGGL((step_kernel<Q, PREC, NS, false, false, COLL_CUM1, MODE, true>), dim3(nblocks), dim3(256),
-                             lds, st, to_kargs<R>(a));
-          break;
-        }
+        run(std::false_type{}, segment);
+      };
+      if constexpr (seg && free) {                     // never with curved walls
+        run_pull(std::true_type{});
+      } else if constexpr (seg) {
+        if (a.lvl) run_pull(std::false_type{});
+        else run_pull(std::true_type{});
+      } else {
+        run_pull(std::false_type{});
       }
-      hipLaunchKernelGGL((step_kernel<Q, PREC, NS, false, FULL, COLL_CUM1, MODE>), dim3(nblocks), dim3(256), lds, st,
-                         to_kargs<R>(a));
       break;
     }
     case COLL_CUM:
@@ -135,6 +137,17 @@ hipError_t launch_split(const StepArgs &a, int nblocks, hipStream_t st) {
   return hipGetLastError();
 }
 
+// The instances of a split step: the list FULL with curved walls, observables or mixture
+// transport, the tiles with the latter two.  Fewer than two scalars split for curved walls alone.
+template <int PREC, int NS, int IMODE>
+hipError_t launch_split_kind(const StepArgs &a, int nblocks, hipStream_t st) {
+  if (a.stats || a.probe_out || a.mix) return launch_split<PREC, NS, true, true, IMODE>(a, nblocks, st);
+  if constexpr (NS >= 2) {
+    if (!a.lvl) return launch_split<PREC, NS, false, false, IMODE>(a, nblocks, st);
+  }
+  return launch_split<PREC, NS, true, false, IMODE>(a, nblocks, st);
+}
+
 template <int Q, int PREC, int NS>
 hipError_t launch_one(int kind, const StepArgs &a, int nblocks, hipStream_t st, const double *Ph,
                       const double *u, const double *scal) {
@@ -146,35 +159,35 @@ hipError_t launch_one(int kind, const StepArgs &a, int nblocks, hipStream_t st, 
       // no boundary anywhere: no boundary code (us per step, all-cell / free instance: vortex
       // 128^2 FP64 6.0 / 4.8, HIT 100^3 FP16 storage 29.3 / 28.3, 128^3 FP32 90.8 / 84.9)
       // (not the FP64 step with a scalar: 48^3 12.3 / 12.9, 128^3 equal)
-      if (without_boundaries(a) && !(PREC == 0 && NS == 1))
-        return a.band_rows ? launch_step<Q, PREC, NS, false, MODE_FREE>(a, nblocks, st)
-                           : launch_step<Q, PREC, NS, false, MODE_FREE_LIN>(a, nblocks, st);
+      if constexpr (!(PREC == 0 && NS == 1)) {
+        if (without_boundaries(a))
+          return a.band_rows ? launch_step<Q, PREC, NS, false, MODE_FREE>(a, nblocks, st)
+                             : launch_step<Q, PREC, NS, false, MODE_FREE_LIN>(a, nblocks, st);
+      }
       return launch_step<Q, PREC, NS, false, MODE_ALL>(a, nblocks, st);
     case LAUNCH_STEP_SPLIT:      // interior cells FULL with observables or mixture transport
-      if constexpr (Q == 9) {
-        const bool ifull = a.stats || a.probe_out || a.mix;
-        if (a.band_rows)
-          return ifull  ? launch_split<PREC, NS, true, true, MODE_INTERIOR>(a, nblocks, st)
-                 : full ? launch_split<PREC, NS, true, false, MODE_INTERIOR>(a, nblocks, st)
-                        : launch_split<PREC, NS, false, false, MODE_INTERIOR>(a, nblocks, st);
-        return ifull  ? launch_split<PREC, NS, true, true, MODE_INTERIOR_LIN>(a, nblocks, st)
-               : full ? launch_split<PREC, NS, true, false, MODE_INTERIOR_LIN>(a, nblocks, st)
-                      : launch_split<PREC, NS, false, false, MODE_INTERIOR_LIN>(a, nblocks, st);
-      }
+      if constexpr (Q == 9)
+        return a.band_rows ? launch_split_kind<PREC, NS, MODE_INTERIOR>(a, nblocks, st)
+                           : launch_split_kind<PREC, NS, MODE_INTERIOR_LIN>(a, nblocks, st);
       return hipErrorInvalidValue;
     case LAUNCH_STEP_INTERIOR:   // on the 64x4 tile grid when it fits, else on linear tiles
       if constexpr (Q == 27) {
-        if (a.band_rows)
-          return a.mix ? launch_step<Q, PREC, NS, true, MODE_INTERIOR>(a, nblocks, st)
-                       : launch_step<Q, PREC, NS, false, MODE_INTERIOR>(a, nblocks, st);
-        return a.mix ? launch_step<Q, PREC, NS, true, MODE_INTERIOR_LIN>(a, nblocks, st)
-                     : launch_step<Q, PREC, NS, false, MODE_INTERIOR_LIN>(a, nblocks, st);
+        if constexpr (NS == 6) {
+          if (a.mix)
+            return a.band_rows ? launch_step<Q, PREC, NS, true, MODE_INTERIOR>(a, nblocks, st)
+                               : launch_step<Q, PREC, NS, true, MODE_INTERIOR_LIN>(a, nblocks, st);
+        }
+        return a.band_rows ? launch_step<Q, PREC, NS, false, MODE_INTERIOR>(a, nblocks, st)
+                           : launch_step<Q, PREC, NS, false, MODE_INTERIOR_LIN>(a, nblocks, st);
       }
       return hipErrorInvalidValue;
-    case LAUNCH_STEP_LIST:
-      if constexpr (Q == 27)
-        return (a.lvl || a.mix) ? launch_step<Q, PREC, NS, true, MODE_LIST>(a, nblocks, st)
-                                : launch_step<Q, PREC, NS, false, MODE_LIST>(a, nblocks, st);
+    case LAUNCH_STEP_LIST:       // plain only with two scalars or more: the others split for curved walls alone
+      if constexpr (Q == 27) {
+        if constexpr (NS >= 2) {
+          if (!a.lvl && !a.mix) return launch_step<Q, PREC, NS, false, MODE_LIST>(a, nblocks, st);
+        }
+        return launch_step<Q, PREC, NS, true, MODE_LIST>(a, nblocks, st);
+      }
       return hipErrorInvalidValue;
     case LAUNCH_EXTRACT:   // no collision on the extract path
       if (full)
