@@ -491,6 +491,33 @@ static hipError_t build_cell_list(lbm_solver *s) {
   return e;
 }
 
+// Whether the list half of a split D3Q27 step has its blocks placed before the interior half's:
+// where its chain is long against the interior half's time.  A wave of it needs more registers
+// than one interior wave leaves, and behind a full chip of interior blocks it waits for the end
+// of them; elsewhere the interior half only starts later.  Tiles up to which it pays, from
+// cones of 1500 to 38000 tiles (us per step, interior / list half first; "lin": the grid is on
+// linear tiles):
+//  - mixture transport, everywhere: burner 64x64x128 FP32 116 / 88, 128x128x256 420 / 387,
+//    160x160x320 766 / 749, FP64 1843 / 1844; without solids 160x160x320 716 / 715;
+//  - two-step FP64 and FP16 storage, everywhere: FP64 4096 tiles 193 / 162, 16384 599 / 582, 24576
+//    887 / 881, 36864 1372 / 1377; FP16 storage 8192 170 / 134, 36864 554 / 532;
+//  - two-step FP32: lin everywhere (8090 tiles 214 / 182, 37969 672 / 661); on 64x4 tiles 6144 137 /
+//    122, 8192 142 / 149, 16384 300 / 312;
+//  - one-step FP64: 3072 109 / 106, lin 4000 123 / 130, 6144 178 / 185;
+//  - isothermal and passive FP64: on 64x4 tiles 6144 159 / 155 and 166 / 161, 8192 195 / 198 and 197 /
+//    206; lin 4000 119 / 113 and 124 / 116, 5855 181 / 181 and 188 / 190, 8090 236 / 242 and 245 / 254;
+//  - the others FP32 and FP16 storage: FP32 isothermal 8192 122 / 117, 10240 133 / 135, passive 8192 127 /
+//    121, 16384 205 / 215, one-step 8192 127 / 122, 10240 145 / 152; FP16 storage one-step 8192 106 /
+//    101, 10240 113 / 119, isothermal 8192 98 / 83, lin 13500 111 / 116.
+// Without curved walls the list is short: reacting box 160x160x320 507 / 517, 121x121x242 303 / 307.
+static bool list_half_first(const lbm_solver *s, const StepArgs &a) {
+  if (a.mix) return true;
+  if (!a.lvl) return false;
+  if (s->NS == 6) return s->prec != LBM_FP32 || !a.band_rows || s->nblocks <= 7000;
+  if (s->prec != LBM_FP64) return s->nblocks <= 8192;
+  return s->nblocks <= (s->NS == 2 ? 3500 : a.band_rows ? 7000 : 5000);
+}
+
 // One step from a.pop_in / a.scal_in, either as one instance over every cell or split into
 // the interior cells of the tile grid and the listed boundary cells.  The split pays where
 // the all-cell instance carries boundary code that costs the interior cells: curved walls
@@ -537,14 +564,8 @@ static hipError_t launch_step_pass(lbm_solver *s, const StepArgs &a0) {
   }
   // fork and join: one half on the caller's stream, the other on the side stream, which waits
   // for everything before this step; the two write disjoint cells and records.  The half on
-  // the caller's stream has its blocks placed first.  That is the list half where its chain
-  // is long against the interior half's time (mixture transport, and curved walls up to 8192
-  // tiles): a wave of it needs more registers than one interior wave leaves, and behind a
-  // full chip of interior blocks it waited for the end of them.  Elsewhere the interior half
-  // would only start later.  us per step, interior / list half first: burner (both)
-  // 128x128x256 419 / 389, 64x64x128 119 / 89, mixture 128^3 203 / 192; cone 64x64x128 FP64 134 /
-  // 102, 128x128x256 295 / 312; reacting box 160x160x320 507 / 517, 121x121x242 303 / 307.
-  const bool list_first = a.mix || (a.lvl && s->nblocks <= 8192);
+  // the caller's stream has its blocks placed first.
+  const bool list_first = list_half_first(s, a);
   const hipStream_t list_stream = list_first ? s->stream : s->side, tile_stream = list_first ? s->side : s->stream;
   StepArgs b = a;
   b.cells = s->cells;
