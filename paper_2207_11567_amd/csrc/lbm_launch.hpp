@@ -72,22 +72,23 @@ hipError_t launch_step(const StepArgs &a, int nblocks, hipStream_t st) {
     case COLL_CUM1: {
       constexpr bool free = MODE == MODE_FREE || MODE == MODE_FREE_LIN;
       constexpr bool inter = MODE == MODE_INTERIOR || MODE == MODE_INTERIOR_LIN;
-      // FP32 and FP64 steps without boundaries: dynamic LDS leaves five blocks a CU instead of
-      // eight (FP32) or six (FP64).
-      // More waves in flight than the memory side needs cost it locality (HIT FP32, us per step
-      // at 8 / 7 / 6 / 5 / 4 blocks: 256^3 667 / 660 / 646 / 643 / 643, 128^3 87.9 / 87.1 / 85.2 /
-      // 84.9 / 85.2; passive 128^3 92.0 / 91.9 / 90.2 / 90.8 / 90.6).  FP16 storage, bound by
-      // issue, wants them all (377 / 380 / 396 / 422 / 425).  FP64 at 6 / 5 / 3: 256^3 1404 / 1338 /
-      // 1323, 224^3 936 / 930 / 935, 128^3 166.7 / 167.4 / 165.1 (all-cell instance, five by its
-      // registers: 1358, 922, 169.8).
-      // Grids of a few passes gain nothing and a single pass loses (passive 64^3 FP32 12.8 / 14.1, HIT 64^3 FP64 25.5 /
-      // 28.7).
-      const unsigned lds = Q == 27 && PREC != 2 && free && nblocks >= 4096 ? 14000 : 0;
+      // FP32 steps without boundaries: dynamic LDS beside the 18432 B of the block sums leaves four
+      // blocks a CU (160 KiB of LDS, given out in units of 1280 B) instead of up to eight.  More waves in
+      // flight than the memory side needs cost it locality: HIT, us per step at 8 / 7 / 6 / 5 / 4 / 3
+      // blocks, 256^3 667 / 663 / 656 / 650 / 649 / 655, 512x128x512 1348 / 1350 / 1340 / 1322 / 1316 /
+      // 1362; at 8 / 5 / 4, 128^3 88.0 / 85.8 / 85.7, 300^3 1159 / 1154 / 1148, passive 256x256x512 1421 /
+      // 1409 / 1376.  From 4096 tiles: 2304 26.3 / 26.3 / 26.9, 3072 37.9 / 36.8 / 37.6, 4096 44.7 / 43.4 /
+      // 43.7.  Of some fifty grids above the line a few lost, by 0.3 to 1.2 % (passive 128^3 91.3 / 91.2 /
+      // 92.4, HIT 224^3 485 / 489 / 489); 512x256x256 gained or lost 4 % (1368 / 1322 / 1313, 1333 / 1359 /
+      // 1384) with the place of its buffers.  FP16 storage, bound by issue, wants all its waves (HIT
+      // 256^3 377 / 396 / 422).
+      const unsigned lds = Q == 27 && PREC == 1 && free && nblocks >= 4096 ? 14000 : 0;
       // SEG by kind of step, not by size, so that a grid rounds as its copies side by side do
       constexpr bool seg = Q == 27 && ((PREC != 0 && NS == 6 && inter) || (PREC == 2 && free)) && !FULL;
       // The plain instances also come with cached pull loads (large grids): the interior ones, and
-      // with fewer than two scalars those of every cell (more scalars split on such grids).
-      constexpr bool cached = !FULL && MODE != MODE_LIST && (inter || NS < 2);
+      // with fewer than two scalars those of every cell (more scalars split on such grids), but
+      // for the boundary-free FP64 one of D3Q27, which serves small grids.
+      constexpr bool cached = !FULL && MODE != MODE_LIST && (inter || NS < 2) && !(free && Q == 27 && PREC == 0);
       auto run = [&](auto pullc, auto segment) {
         hipLaunchKernelGGL((step_kernel<Q, PREC, NS, false, FULL, COLL_CUM1, MODE, decltype(pullc)::value,
                                         decltype(segment)::value>), dim3(nblocks), dim3(256), lds, st, to_kargs<R>(a));
@@ -156,11 +157,14 @@ hipError_t launch_one(int kind, const StepArgs &a, int nblocks, hipStream_t st, 
   switch (kind) {
     case LAUNCH_STEP:
       if (full) return launch_step<Q, PREC, NS, true, MODE_ALL>(a, nblocks, st);
-      // no boundary anywhere: no boundary code (us per step, all-cell / free instance: vortex
-      // 128^2 FP64 6.0 / 4.8, HIT 100^3 FP16 storage 29.3 / 28.3, 128^3 FP32 90.8 / 84.9)
-      // (not the FP64 step with a scalar: 48^3 12.3 / 12.9, 128^3 equal)
+      // No boundary anywhere: no boundary code (us per step, all-cell / free instance: vortex
+      // 128^2 FP64 6.0 / 4.8, HIT 100^3 FP16 storage 28.2 / 27.4, 32^3 FP32 6.6 / 5.9, two-step 64^3 FP64
+      // 48 / 38).  In FP64 not with one scalar (48^3 12.3 / 12.8, 128^3 181 / 182, 256x256x192 1068 /
+      // 1059), and on D3Q27 isothermal up to 4096 tiles (32^3 7.9 / 7.2, 64^3 24.8 / 24.3, 128x64x96 71.4 /
+      // 71.0, 128x128x64 87.6 / 88.0; 125^3 192.0 / 194.1, 192^3 597 / 600, 250^3 1368 / 1386, 256^3 1327 /
+      // 1332, and no better with fewer resident blocks: 125^3 195, 192^3 602, 250^3 1384, 256^3 1321).
       if constexpr (!(PREC == 0 && NS == 1)) {
-        if (without_boundaries(a))
+        if (without_boundaries(a) && (Q != 27 || PREC != 0 || nblocks <= 4096))
           return a.band_rows ? launch_step<Q, PREC, NS, false, MODE_FREE>(a, nblocks, st)
                              : launch_step<Q, PREC, NS, false, MODE_FREE_LIN>(a, nblocks, st);
       }
