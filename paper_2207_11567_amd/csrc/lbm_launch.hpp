@@ -159,11 +159,11 @@ hipError_t launch_one(int kind, const StepArgs &a, int nblocks, hipStream_t st, 
       if (full) return launch_step<Q, PREC, NS, true, MODE_ALL>(a, nblocks, st);
       // No boundary anywhere: no boundary code (us per step, all-cell / free instance: vortex
       // 128^2 FP64 6.0 / 4.8, HIT 100^3 FP16 storage 28.2 / 27.4, 32^3 FP32 6.6 / 5.9, two-step 64^3 FP64
-      // 48 / 38).  In FP64 not with one scalar (48^3 12.3 / 12.8, 128^3 181 / 182, 256x256x192 1068 /
-      // 1059), and on D3Q27 isothermal up to 4096 tiles (32^3 7.9 / 7.2, 64^3 24.8 / 24.3, 128x64x96 71.4 /
+      // 48 / 38).  D3Q27 in FP64: not with one scalar (48^3 12.3 / 12.8, 128^3 181 / 182, 256x256x192
+      // 1068 / 1059), and isothermal up to 4096 tiles (32^3 7.9 / 7.2, 64^3 24.8 / 24.3, 128x64x96 71.4 /
       // 71.0, 128x128x64 87.6 / 88.0; 125^3 192.0 / 194.1, 192^3 597 / 600, 250^3 1368 / 1386, 256^3 1327 /
       // 1332, and no better with fewer resident blocks: 125^3 195, 192^3 602, 250^3 1384, 256^3 1321).
-      if constexpr (!(PREC == 0 && NS == 1)) {
+      if constexpr (!(Q == 27 && PREC == 0 && NS == 1)) {
         if (without_boundaries(a) && (Q != 27 || PREC != 0 || nblocks <= 4096))
           return a.band_rows ? launch_step<Q, PREC, NS, false, MODE_FREE>(a, nblocks, st)
                              : launch_step<Q, PREC, NS, false, MODE_FREE_LIN>(a, nblocks, st);
