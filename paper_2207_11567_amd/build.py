@@ -24,16 +24,14 @@ FLAGS = ["-std=c++17", "-O3", f"--offload-arch={ARCH}", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include")]
 
-UNITS = ["lbm_capi.hip", "lbm_d2q9.hip", "lbm_d3q27.hip", "lbm_d3q27_p0.hip",
-         "lbm_d3q27_p1.hip", "lbm_d3q27_p2.hip", "lbm_adjoint.hip"]
-
+UNITS = ["lbm_capi.hip", "lbm_d2q9.hip", "lbm_d3q27.hip", "lbm_adjoint.hip"]
 
 _ARGS = "(int, const StepArgs &, int, hipStream_t, const double *, const double *, const double *)"
 
 
 def _instances():
-    """{unit: [extra flags]} of the generated instance units, written to _build/, and the header
-    that declares them to the dispatching units; the longest compilations first."""
+    """Paths of the generated instance units, the longest compilations first; writes them and the
+    header that declares them to the dispatching units to _build/."""
     combos = [(q, p, n) for n in (6, 2, 1, 0) for q in (27, 9) for p in (0, 2, 1)]
     head = f'#include "{CSRC}/lbm_launch.hpp"\n'
 
@@ -53,7 +51,7 @@ def _instances():
 def _compile(src):
     obj = os.path.join(BUILD, os.path.basename(src).replace(".hip", ".o"))
     cmd = [HIPCC] + FLAGS + ["-c", src, "-o", obj]
-    if "lbm_d2q9" in src or "lbm_d3q27" in src:
+    if os.path.basename(src) in ("lbm_d2q9.hip", "lbm_d3q27.hip"):
         cmd += ["-include", os.path.join(BUILD, "instances.hpp")]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

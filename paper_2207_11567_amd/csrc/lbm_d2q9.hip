@@ -1,4 +1,5 @@
-// D2Q9 instances of the fused step (all precisions and scalar counts).
+// D2Q9 dispatch over precisions and scalar counts (the instances are generated units, one per
+// precision and number of scalars), and the launches of the kernels that both lattices share.
 #include "lbm_launch.hpp"
 
 namespace lbm {

@@ -1,5 +1,5 @@
-// Host-side launch entry points of the step kernels, one set per (lattice, precision,
-// scalar count) instance; defined in the per-lattice translation units.
+// Host-side launch entry points, and the choice of a step's instance from its arguments
+// (launch_one, instantiated per lattice, precision and number of scalars in generated units).
 #pragma once
 
 #include "lbm_step.hpp"
