@@ -31,14 +31,18 @@ __device__ __forceinline__ unsigned adjoint_source(unsigned un, int i, const int
 }
 
 // One reverse step of a cell.  Bound by memory: the populations, their adjoint in and out, and
-// the 13 coefficients of the scalar (440 B per FP32 cell) at two waves per SIMD (three 27-vectors
-// live; asked for three waves it spills and takes 225 us).  All accesses are raw buffer ones
-// with shared 32-bit offsets, the stencil loads its three upwind neighbours instead of four, and
-// FP32 streams the incoming adjoint, which is read once (FP64, at one wave, measured slower
-// so).  FP32 us per step, passive 128^3 198 -> 190 (4.9 TB/s), isothermal 128^3 153 -> 142,
-// passive 100x90x110 101 -> 93, 40^3 13.1 -> 11.6; on the step's 64x4 tiles with scalar y and
-// z the passive one took 204.
-template <int PREC, int NS>
+// the 13 coefficients of the scalar (440 B per FP32 cell) at two waves per SIMD in FP32 (three
+// 27-vectors live; asked for three waves it spills and takes 225 us) and one in FP64.  The pull
+// takes raw buffer loads with shared 32-bit offsets, everything after it plain accesses: as
+// buffer ones the loads could not pass the stores of the coefficients, and the axes waited for
+// one another.  The stencil's neighbours: in FP32 all four of each axis, loaded before the velocity
+// is known; in FP64, where registers are short, the three upwind ones.  NT streams the incoming
+// adjoint, which is read once (FP32 where the step's arrays exceed the Infinity Cache, below).
+// us per step, global loads in linear order / this: FP32 passive 128^3 195 / 186 (5.0 TB/s), 100x90x110
+// 99 / 87, 64^3 26.0 / 25.5, 48^3 14.8 / 13.4, isothermal 128^3 145 / 139, 64^3 18.7 / 18.2; FP64 passive 128^3
+// 427 / 422, 128x96x96 233 / 236, 64^3 46.5 / 46.9, 48^3 26.1 / 25.7, 24^3 12.0 / 12.0.  On the step's 64x4
+// tiles with scalar y and z the FP32 passive one took 204 at 128^3.
+template <int PREC, int NS, bool NT>
 __global__ __launch_bounds__(256) void adjoint_kernel(KArgs<typename Prec<PREC>::R> a,
                     const typename Prec<PREC>::R *__restrict__ lamB,
                     const typename Prec<PREC>::R *__restrict__ lamT1, typename Prec<PREC>::R *__restrict__ lamA,
@@ -54,11 +58,18 @@ __global__ __launch_bounds__(256) void adjoint_kernel(KArgs<typename Prec<PREC>:
   if (n >= N) return;
   const unsigned un = (unsigned)n;
   const St *__restrict__ pin = (const St *)a.pop_in;
-  const auto sT = slice(a.scal_in);
+  const Sc *__restrict__ T = (const Sc *)a.scal_in;
   // pull (forward recompute)
   R g[27];
 #pragma unroll
   for (int i = 0; i < 27; ++i) g[i] = decode<R>(bld<St>(slice(pin + (size_t)i * N), adjoint_source(un, i, off)));
+  R nb[3][4];                                       // the scalar at -2, -1, +1, +2 per axis
+  if constexpr (NS == 1 && PREC != 0) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) nb[d][k] = (R)ldg(T, un + (unsigned)off[d][k < 2 ? k : k + 1]);
+  }
   const R rho0 = a.th.rho_ref;
   const R mom = fdiv(a.P0, s * rho0);
   R mx = R(0), my = R(0), mz = R(0);
@@ -72,34 +83,41 @@ __global__ __launch_bounds__(256) void adjoint_kernel(KArgs<typename Prec<PREC>:
   R lu[3] = {R(0), R(0), R(0)};
   if constexpr (NS == 1) {
     // T' = T + K lap T - sum_d |u_d| W_d: adjoint of the advection part, per axis
-    const R T0 = (R)bld<Sc>(sT, un);
-    const R lT = bld<R>(slice(lamT1), un);
+    const R T0 = (R)ldg(T, un);
+    const R lT = lamT1[n];
     R self = R(0);
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       const bool up = u[d] >= R(0);
-      // the three upwind-ordered neighbours of the stencil
-      const R U1 = (R)bld<Sc>(sT, un + (unsigned)(up ? off[d][1] : off[d][3]));
-      const R D1 = (R)bld<Sc>(sT, un + (unsigned)(up ? off[d][3] : off[d][1]));
-      const R U2 = (R)bld<Sc>(sT, un + (unsigned)(up ? off[d][0] : off[d][4]));
+      R U1, D1, U2;                                 // the upwind-ordered neighbours of the stencil
+      if constexpr (PREC != 0) {
+        U1 = up ? nb[d][1] : nb[d][2];
+        D1 = up ? nb[d][2] : nb[d][1];
+        U2 = up ? nb[d][0] : nb[d][3];
+      } else {
+        U1 = (R)ldg(T, un + (unsigned)(up ? off[d][1] : off[d][3]));
+        D1 = (R)ldg(T, un + (unsigned)(up ? off[d][3] : off[d][1]));
+        U2 = (R)ldg(T, un + (unsigned)(up ? off[d][0] : off[d][4]));
+      }
       R dW[4];
       const R W = weno3_diff_grad(U2, U1, T0, D1, a.eps[0], dW);
       lu[d] += up ? -lT * W : lT * W;               // d(-|u| W)/du = -sign(u) W
       const R c = -lT * fabs(u[d]);
       // contributions to the positions -2, -1, +1, +2 along d (and to the cell itself)
       const R cU2 = c * dW[0], cU1 = c * dW[1], cD1 = c * dW[3];
-      bst<R>(slice(coef + (size_t)(4 * d + 0) * N), un, up ? cU2 : R(0));
-      bst<R>(slice(coef + (size_t)(4 * d + 1) * N), un, up ? cU1 : cD1);
-      bst<R>(slice(coef + (size_t)(4 * d + 2) * N), un, up ? cD1 : cU1);
-      bst<R>(slice(coef + (size_t)(4 * d + 3) * N), un, up ? R(0) : cU2);
+      coef[(size_t)(4 * d + 0) * N + n] = up ? cU2 : R(0);
+      coef[(size_t)(4 * d + 1) * N + n] = up ? cU1 : cD1;
+      coef[(size_t)(4 * d + 2) * N + n] = up ? cD1 : cU1;
+      coef[(size_t)(4 * d + 3) * N + n] = up ? R(0) : cU2;
       self += c * dW[2];
     }
-    bst<R>(slice(coef + (size_t)12 * N), un, self);
+    coef[(size_t)12 * N + n] = self;
   }
   // collision reverse pass
   R lam[27];
 #pragma unroll
-  for (int i = 0; i < 27; ++i) lam[i] = bld<R, PREC == 0 ? 0 : 2>(slice(lamB + (size_t)i * N), un);
+  for (int i = 0; i < 27; ++i)
+    lam[i] = NT ? __builtin_nontemporal_load(lamB + (size_t)i * N + n) : lamB[(size_t)i * N + n];
   Rates<R> rt;
   rt.tau0 = viscosity(a.th, rho0) * R(3) + R(0.5);
   rt.smag18 = a.smag18;
@@ -110,7 +128,7 @@ __global__ __launch_bounds__(256) void adjoint_kernel(KArgs<typename Prec<PREC>:
   collide_d3q27_vjp(g, mom, rt, lam, lu);
   // transposed streaming: the adjoint of g_i(r) = A_i(r - c_i) is pushed to r - c_i
 #pragma unroll
-  for (int i = 0; i < 27; ++i) bst<R>(slice(lamA + (size_t)i * N), adjoint_source(un, i, off), lam[i]);
+  for (int i = 0; i < 27; ++i) stg(lamA + (size_t)i * N, adjoint_source(un, i, off), lam[i]);
 }
 
 // lamT(s) = lamT'(s) + K lap(lamT')(s) + self(s) + gathered advection contributions.
@@ -226,12 +244,25 @@ hipError_t launch_adjoint_p(int ns, int kind, const StepArgs &sa, int nblocks, h
   using R = typename Prec<PREC>::R;
   KArgs<R> a = to_kargs<R>(sa);
   if (kind == 0) {   // adjoint step
+    // XCD order where there is more than about a block a CU: a few blocks gain nothing from shared
+    // planes and pay for the order (us per step, linear / XCD order: FP64 24^3 12.0 / 12.5, 40^3 16.2 /
+    // 15.7, 80^3 110 / 100)
+    a.remap = nblocks > 192;
+    // NT: FP32 steps whose arrays exceed the 256 MB Infinity Cache.  Those of a smaller grid stay
+    // there from one reverse step to the next (us per step, kept / streamed: passive 64^3 25.7 /
+    // 27.0, 96x64x96 (260 MB) 47.2 / 52.4, 96^3 (389 MB) 78.9 / 72.5, 128^3 191.7 / 187.9; isothermal
+    // 96x64x96 33.8 / 37.6, 96^3 (287 MB) 57.1 / 52.3, 128^3 141.9 / 138.5; FP64 passive 128^3 435 / 447)
+    const size_t bytes = (size_t)sa.N * sizeof(R) * (ns ? 110 : 81);
+    const bool nt = PREC != 0 && bytes > ((size_t)256 << 20);
+    auto run = [&](auto scalars, auto stream) {
+      hipLaunchKernelGGL((adjoint_kernel<PREC, decltype(scalars)::value, PREC != 0 && decltype(stream)::value>),
+                         dim3(nblocks), dim3(256), 0, st, a, (const R *)p0, (const R *)p1, (R *)p2, (R *)p4);
+    };
+    auto run_ns = [&](auto scalars) { nt ? run(scalars, std::true_type{}) : run(scalars, std::false_type{}); };
     if (ns == 0) {
-      hipLaunchKernelGGL((adjoint_kernel<PREC, 0>), dim3(nblocks), dim3(256), 0, st, a, (const R *)p0, (const R *)p1,
-                         (R *)p2, (R *)p4);
+      run_ns(std::integral_constant<int, 0>{});
     } else {
-      hipLaunchKernelGGL((adjoint_kernel<PREC, 1>), dim3(nblocks), dim3(256), 0, st, a, (const R *)p0, (const R *)p1,
-                         (R *)p2, (R *)p4);
+      run_ns(std::integral_constant<int, 1>{});
       hipLaunchKernelGGL((adjoint_scalar_kernel<PREC>), dim3(nblocks), dim3(256), 0, st, a, (const R *)p1, (const R *)p4,
                          (R *)p3);
     }
