@@ -455,33 +455,30 @@ static lbm_status check_flag(lbm_solver *s) {
 // interior instance).  Built on the host from the geometry words; synchronises.
 static bool host_near_face(int c, int n, int flo, int fhi) { return (flo >= 0 && c < 2) || (fhi >= 0 && c >= n - 2); }
 
-static hipError_t build_cell_list(lbm_solver *s) {
+template <class Word> static hipError_t build_cell_list(lbm_solver *s) {
   const lbm_params &p = s->p;
-  StepArgs a = make_args(s);
-  const long long N = s->N;
-  const size_t gsz = s->Q == 9 ? 4 : 8;
-  std::vector<unsigned char> gw;
+  const StepArgs a = make_args(s);
+  std::vector<Word> gw;
   hipError_t e = hipSuccess;
   if (s->has_geom) {
-    gw.resize((size_t)N * gsz);
-    e = hipMemcpyAsync(gw.data(), s->geom, gw.size(), hipMemcpyDeviceToHost, s->stream);
+    gw.resize((size_t)s->N);
+    e = hipMemcpyAsync(gw.data(), s->geom, gw.size() * sizeof(Word), hipMemcpyDeviceToHost, s->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) return e;
   }
+  // x below lo and from hi on lies near a face; between them the geometry word decides
+  const int lo = a.face[0] >= 0 ? std::min(2, p.nx) : 0, hi = a.face[1] >= 0 ? std::max(p.nx - 2, lo) : p.nx;
   std::vector<int> list;
   for (int z = 0; z < p.nz; ++z)
     for (int y = 0; y < p.ny; ++y) {
+      const int n0 = p.nx * (y + p.ny * z);
       const bool row = host_near_face(y, p.ny, a.face[2], a.face[3]) || host_near_face(z, p.nz, a.face[4], a.face[5]);
-      if (!row && !s->has_geom && a.face[0] < 0 && a.face[1] < 0) continue;     // all of it interior
-      for (int x = 0; x < p.nx; ++x) {
-        const long long n = x + (long long)p.nx * (y + (long long)p.ny * z);
-        bool g = row || host_near_face(x, p.nx, a.face[0], a.face[1]);
-        if (!g && s->has_geom) {
-          const unsigned char *w = gw.data() + (size_t)n * gsz;
-          for (size_t b = 0; b < gsz; ++b) g = g || w[b] != 0;
-        }
-        if (g) list.push_back((int)n);
-      }
+      const int first = row ? p.nx : lo, last = row ? p.nx : hi;
+      for (int x = 0; x < first; ++x) list.push_back(n0 + x);
+      if (s->has_geom)
+        for (int x = first; x < last; ++x)
+          if (gw[(size_t)n0 + x] != 0) list.push_back(n0 + x);
+      for (int x = last; x < p.nx; ++x) list.push_back(n0 + x);
     }
   s->ncells = (int)list.size();
   if (!list.empty()) {
@@ -489,6 +486,10 @@ static hipError_t build_cell_list(lbm_solver *s) {
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
   }
   return e;
+}
+
+static hipError_t build_cell_list(lbm_solver *s) {
+  return s->Q == 9 ? build_cell_list<GeomWord<9>::T>(s) : build_cell_list<GeomWord<27>::T>(s);
 }
 
 // Whether the list half of a split D3Q27 step has its blocks placed before the interior half's:
