@@ -70,6 +70,14 @@ __device__ __forceinline__ float hlog2(float x) { return __builtin_amdgcn_logf(x
 __device__ __forceinline__ double hsqrt(double x) { return sqrt(x); }
 __device__ __forceinline__ float hsqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
 
+// a - b of two rounded values.  Where a is a product the compiler may otherwise contract it into
+// the difference, unrounded against a rounded b, and two equal values then differ by the
+// rounding: a density gradient or a diffusive flux in a uniform gas, which drifts in mass.
+template <class R> __device__ __forceinline__ R difference(R a, R b) {
+#pragma clang fp contract(off)
+  return a - b;
+}
+
 // ------------------------------------------------------------------------ 1-D chimera
 // Central moments of orders 0,1,2 about u of a 3-point distribution on {-1,0,+1}
 // (Geier et al. 2015, the 1-D factor of the D2Q9/D3Q27 moment transform), in place.

@@ -425,8 +425,7 @@ constexpr int step_waves_per_eu() {
 }
 // SEG: the arguments are read where the launch put them, through step_cells, instead of as the
 // kernel's parameter; the same formulas, another register allocation (118 instead of 112
-// VGPRs, other places of the loads, other contractions; reacting box FP32, 12 steps: the same error
-// against 64 bits, 7.0e-7).  Measured per kind of step: faster for the interior cells of
+// VGPRs, other places of the loads).  Measured per kind of step: faster for the interior cells of
 // the two-step step (reacting box 192x192x384 FP32 843 -> 827 us, FP16 storage 713 -> 681) and
 // for HIT 256^3 with FP16 storage (378 -> 365), slower beside the curved-wall list (cone
 // 128x128x256 298 -> 330: its waves no longer fit beside three interior ones).
@@ -450,43 +449,19 @@ void step_kernel(KArgs<typename Prec<PREC>::R> a) {
 // 8, so that the tiles' blocks keep their XCDs) update the listed boundary cells, the others
 // the interior cells of their tile.  Both kinds need the same registers here, so one
 // kernel costs no occupancy, the long boundary chains start first and end under the interior
-// ones, and nothing waits for another stream's event.
-// FP32 arithmetic has the two bodies in the kernel itself, on its parameter: read from the argument
-// segment through step_cells the compiler contracts other products, and the populations came out
-// 12 to 17 % further from 64-bit ones (flame 2048x512, 24 steps: relative error 5.4e-7 instead of
-// 4.6e-7), for the same time (31 us per step).  FP64 shows no such difference and is faster through
-// step_cells (chamber 2500x500 62 us per step, 65 the other way).
-template <int PREC, int NS, bool LFULL, bool IFULL, int COLL, int IMODE, bool IPULLC>
-__global__ __launch_bounds__(256) void split_kernel(KArgs<typename Prec<PREC>::R> a) {
+// ones, and nothing waits for another stream's event. 
+template <int PREC, int NS, bool LFULL, bool IFULL, int COLL, int IMODE, bool PULLC>
+__global__ __launch_bounds__(256) void split_kernel(KArgs<typename Prec<PREC>::R>) {
+  const auto &a = kernel_args<typename Prec<PREC>::R>();
   double red[NSUM] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+  const int block = (int)blockIdx.x - a.nlb, ntiles = (int)gridDim.x - a.nlb;
   int rec;
-  if constexpr (PREC == 0) {
-    const auto &ka = kernel_args<typename Prec<PREC>::R>();
-    const int block = (int)blockIdx.x - ka.nlb, ntiles = (int)gridDim.x - ka.nlb;
-    if (block < 0)
-      rec = ntiles + step_cells<9, PREC, NS, false, LFULL, COLL, MODE_LIST, false>(ka, blockIdx.x, ka.nlb, red);
-    else
-      rec = step_cells<9, PREC, NS, false, IFULL, COLL, IMODE, IPULLC>(ka, block, ntiles, red);
-    block_sums(red, ka.partials + (size_t)rec * NSUM);
+  if (block < 0) {
+    rec = ntiles + step_cells<9, PREC, NS, false, LFULL, COLL, MODE_LIST, false>(a, blockIdx.x, a.nlb, red);
   } else {
-    constexpr int Q = 9;
-    constexpr bool EXTRACT = false;
-    const int ntiles = (int)gridDim.x - a.nlb;
-    if ((int)blockIdx.x < a.nlb) {
-      constexpr int MODE = MODE_LIST;
-      constexpr bool FULL = LFULL, PULLC = false;
-      const int block = (int)blockIdx.x, nblocks = a.nlb;
-#include "lbm_step_cells.inc"
-      rec = ntiles + tile;
-    } else {
-      constexpr int MODE = IMODE;
-      constexpr bool FULL = IFULL, PULLC = IPULLC;
-      const int block = (int)blockIdx.x - a.nlb, nblocks = ntiles;
-#include "lbm_step_cells.inc"
-      rec = tile;
-    }
-    block_sums(red, a.partials + (size_t)rec * NSUM);
+    rec = step_cells<9, PREC, NS, false, IFULL, COLL, IMODE, PULLC>(a, block, ntiles, red);
   }
+  block_sums(red, a.partials + (size_t)rec * NSUM);
 }
 
 // The first bytes of the work buffer (divergence flag at 0, final sums at 64, thermodynamic
