@@ -519,19 +519,37 @@ static bool list_half_first(const lbm_solver *s, const StepArgs &a) {
   return s->nblocks <= (s->NS == 2 ? 3500 : a.band_rows ? 7000 : 5000);
 }
 
+// Whether a D2Q9 step runs split: with curved walls, but for observed steps of fewer than two
+// scalars (160x100 FP32 isothermal 10.3 us as one instance, 15.5 split, 2048x512 39.4 / 39.3); with
+// two or more scalars where the tiles need more than one pass over the chip (256 CUs of 4
+// resident blocks in FP64, 8 otherwise; within one pass the step takes the latency of its longest
+// wave and the extra blocks only add to it), in FP32 with two scalars from a little later, where
+// the one instance's own boundary code is short.  us per step, one instance / split, for flames,
+// chambers, a channel with inlet and outlet and a porous one:
+//  - one-step FP64, 1040 tiles 22.8 / 20.7, 25.6 / 22.8, 22.0 / 21.4, 20.6 / 22.7; 1600 26.4 / 23.5, 31.4 /
+//    26.7, 25.8 / 23.2, 30.4 / 27.5 (1024 tiles: flame 19.1 / 22.4);
+//  - one-step FP16 storage, 2080 tiles 19.4 / 18.7, 22.6 / 24.0, 19.3 / 18.9, 17.7 / 17.4; 4096 28.4 / 24.6, 32.8 /
+//    31.0, 28.1 / 25.0, 29.7 / 27.3;
+//  - one-step FP32 on linear tiles, 2133 19.4 / 21.0, 22.8 / 24.9; 2110 18.7 / 21.4, 18.0 / 23.0; 2813 22.6 /
+//    21.9, 27.2 / 26.2; 3516 27.8 / 24.7, 32.1 / 29.8, 25.9 / 23.8, 26.7 / 28.5; on 64x4 tiles, 3200 23.8 / 24.5,
+//    28.7 / 27.8, 23.4 / 26.4, 26.7 / 28.9; 4096 30.3 / 32.0, 35.1 / 35.4, 30.5 / 32.3, 33.8 / 33.1; 8192 50.0 /
+//    48.1, 55.0 / 56.5;
+//  - two-step, channel: FP64 1040 tiles 37.6 / 25.0, FP32 2080 29.3 / 27.3, FP16 storage 2080 28.4 / 24.2.
+static bool split_d2q9(const lbm_solver *s, const StepArgs &a, bool observed) {
+  if (a.lvl && !observed) return true;
+  if (s->NS < 2) return false;
+  if (s->prec == LBM_FP64) return s->nblocks > 1024;
+  if (s->prec == LBM_FP32 && s->NS == 2) return s->nblocks > (a.band_rows ? 4096 : 2600);
+  return s->nblocks > 2048;
+}
+
 // One step from a.pop_in / a.scal_in, either as one instance over every cell or split into
 // the interior cells of the tile grid and the listed boundary cells.  The split pays where
 // the all-cell instance carries boundary code that costs the interior cells: curved walls
 // (FULL list) and, on large grids, the steps with two or more transported scalars (their
 // stencil ghost rules are most of that code).  The isothermal and passive steps measured
 // slower as interior instances.  Block records: the tiles, then the list blocks.
-// D2Q9 runs both kinds in one launch, observables included, where the tiles need more than
-// one pass over the chip (256 CUs of 4 resident blocks in FP64, 8 in FP32): within one pass
-// the step takes the latency of its longest wave and the extra blocks only add to it.
-// us per step, one instance / split: FP64 flame 1024x256 (1024 tiles) 19.1 / 22.4, chamber
-// 1250x250 (1221) 26.8 / 24.2, flame 1800x400 (2813) 43.9 / 34.7, chamber 2500x500 70.8 / 57.9
-// (67.3 as two kernels on two streams), with statistics 87.0 / 75.0; FP32 flame 1230x310
-// (1490) 15.2 / 17.9, 1800x400 (2813) 24.9 / 20.7, 2048x512 31.9 / 27.9 (50.8 on two streams).
+// D2Q9 runs both kinds in one launch where split_d2q9 says so.
 // D3Q27 runs them as two kernels on two streams from 4096 tiles on (in one kernel the
 // boundary code's registers cost the interior cells their waves: reacting box 0.86 ->
 // 1.02 ms), and its steps with observables stay one FULL instance.
@@ -539,9 +557,8 @@ static hipError_t launch_step_pass(lbm_solver *s, const StepArgs &a0) {
   StepArgs a = a0;
   a.partials = s->partials;
   const bool observed = a.stats || a.probe_out;
-  const int one_pass = s->prec == LBM_FP64 ? 1024 : 2048;
-  const bool large = s->Q == 9 ? s->nblocks > one_pass : s->nblocks >= 4096;
-  const bool split = (s->Q == 9 || !observed) && (a.lvl || (s->NS >= 2 && large));
+  const bool split = s->Q == 9 ? split_d2q9(s, a, observed)
+                               : !observed && (a.lvl || (s->NS >= 2 && s->nblocks >= 4096));
   if (!split) {
     s->nrec = s->nblocks;
     return launch(s, LAUNCH_STEP, a);

@@ -449,9 +449,13 @@ void step_kernel(KArgs<typename Prec<PREC>::R> a) {
 // 8, so that the tiles' blocks keep their XCDs) update the listed boundary cells, the others
 // the interior cells of their tile.  Both kinds need the same registers here, so one
 // kernel costs no occupancy, the long boundary chains start first and end under the interior
-// ones, and nothing waits for another stream's event. 
+// ones, and nothing waits for another stream's event.  With observables or mixture transport in
+// the two-step step the two bodies together took a wave more than one does (FP64 one wave per
+// SIMD instead of two, FP32 three instead of four), so these ask for it: channel 2048x512 with
+// mixture transport FP64 225 -> 145 us per step (163 as one instance), FP32 70 -> 63 (75).
 template <int PREC, int NS, bool LFULL, bool IFULL, int COLL, int IMODE, bool PULLC>
-__global__ __launch_bounds__(256) void split_kernel(KArgs<typename Prec<PREC>::R>) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(IFULL && NS == 6 ? (PREC == 0 ? 2 : 4) : 1)))
+void split_kernel(KArgs<typename Prec<PREC>::R>) {
   const auto &a = kernel_args<typename Prec<PREC>::R>();
   double red[NSUM] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
   const int block = (int)blockIdx.x - a.nlb, ntiles = (int)gridDim.x - a.nlb;
