@@ -108,12 +108,13 @@ def _check(p, ghat, scal, solid, copies, observed):
     s.close()
 
 
-# copies: just over one pass (1024 tiles FP64, 2048 otherwise); 64 x 40 on 64x4 tiles, the
+# copies: just over one pass (1024 tiles FP64, 2048 otherwise), and for FP32 with two scalars also
+# just over the lines it splits from (4096 64x4 tiles, 2600 linear ones); 64 x 40 on 64x4 tiles, the
 # others on linear tiles, the last one partly filled
 @pytest.mark.parametrize("observed", [False, True])
 @pytest.mark.parametrize("nx,ny,copies,precision", [
     (64, 40, 103, "fp64"), (50, 37, 143, "fp64"), (64, 40, 206, "fp32"), (45, 33, 355, "fp32"), (64, 40, 206, "fp16s"),
-    (45, 33, 355, "fp16s"),
+    (45, 33, 355, "fp16s"), (64, 40, 411, "fp32"), (45, 33, 450, "fp32"),
 ])
 @pytest.mark.parametrize("physics,faces", [
     ("one_step", WALLS), ("one_step", OPEN), ("two_step", OPEN), ("mixture", OPEN),
@@ -124,7 +125,7 @@ def test_split_channel_matches_oracle(physics, faces, nx, ny, copies, precision,
     _check(p, ghat, scal, _solids(nx, ny), copies, observed)
 
 
-@pytest.mark.parametrize("nx,ny,copies,precision", [(64, 40, 103, "fp64"), (45, 33, 355, "fp32")])
+@pytest.mark.parametrize("nx,ny,copies,precision", [(64, 40, 103, "fp64"), (45, 33, 355, "fp32"), (45, 33, 450, "fp32")])
 def test_split_bgk_channel_matches_oracle(nx, ny, copies, precision):
     p = _params(nx, ny, "one_step", precision, OPEN, collision="bgk")
     ghat, scal = random_state(p, seed=33)
